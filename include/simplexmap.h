@@ -323,11 +323,13 @@ int simplex_copy_launch(int m, int64_t n, const void *buf_in, void *buf_out, voi
 /* ---- several generations per launch -------------------------------------
  *
  * `steps` generations of the automaton (Section 5.1 runs a fixed number of
- * steps) with temporal blocking: each pass loads a tile plus a halo into
- * LDS and advances it as many generations as the halo is wide, so HBM is
+ * steps) with temporal blocking: each pass loads a tile plus a halo onto
+ * the chip and advances it as many generations as the halo is wide, so HBM is
  * read and written once per pass instead of once per generation.
  * Supported (others: SMAP_EUNSUPPORTED):
- *   m = 2, SMAP_OP_CA2: 256 x 256 tiles, halo 32: up to G = 32 per pass;
+ *   m = 2, SMAP_OP_CA2: tiles of 64 to 240 cells a side inside regions of
+ *     128 or 256 cells, chosen from n and the generations of a pass: up to
+ *     G = 32 per pass;
  *   m = 3, SMAP_OP_CA3: 64^3 tiles, halo 16: up to G = 16 per pass.
  *
  * buf_out receives the state after `steps` generations of buf_in (layout

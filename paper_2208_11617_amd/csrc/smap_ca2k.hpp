@@ -1,52 +1,46 @@
 // smap_ca2k.hpp -- several Life generations (B3/S23) per pass over HBM.
 //
 // The paper's automaton test runs a fixed number of steps (Section 5.1).
-// One launch here advances every cell of Delta_n^2 by `gens` <= KH
-// generations: a workgroup loads its rho x rho tile plus a halo of KH cells
-// on each side into LDS (cells outside the simplex, or outside the box, are
-// dead), steps the whole region `gens` times in LDS, and writes the tile.
-// Each generation the band of cells whose neighbourhood reached outside the
-// loaded region grows inward by one, so after gens <= KH generations the
-// tile itself is exact.  HBM traffic per generation drops from 2 bytes per
-// cell to about ((rho + 2 KH)^2 / rho^2 + 1) / gens.
+// One launch here advances every cell of Delta_n^2 by `gens` <= 32
+// generations: a workgroup takes a rho x rho tile plus a halo of
+// (W - rho) / 2 >= gens cells on each side, W x W cells in all (cells outside
+// the simplex, or outside the box, are dead), steps the whole region `gens`
+// times on chip, and writes the tile.  Each generation the band of cells
+// whose neighbourhood reached outside the region grows inward by one, so
+// after `gens` generations the tile itself is exact.
 //
-// In LDS a cell is one bit: two buffers of (rho + 2 KH) rows x
-// (rho + 2 KH) / 32 dwords; bit b of dword c of row r is the cell
-// x = x0 - KH + 32c + b, y = y0 - KH + r.  The neighbour count is
-// bit-sliced: the horizontal 3-sum of a row is a 2-bit number per cell
-// (a full adder over the row and its copies shifted by one cell, the
-// shifts funnelled across dword boundaries), the 3x3 sum including the
-// centre is the sum of three such numbers (4 bits, at most 9), and the rule
-// is a few logic operations on those bits: 32 cells per operation.  A
-// thread owns one dword column and a run of rows and walks the run with the
-// horizontal sums of the two previous rows in registers.
+// The region lives in registers, one bit per cell: a lane holds a column of
+// R words (32 cells along x each), XL lanes stand side by side along x, and
+// the 64 / XL lane groups of a wave and the waves of the workgroup stand
+// below one another.  A word's neighbours along x come from the next lanes
+// (DPP row shifts; what enters at the region's edge is never used by the
+// tile), the rows above and below a lane's run from the neighbouring groups
+// through LDS, two words each way per generation, with one barrier.  The
+// neighbour count is bit-sliced: a row's horizontal 3-sum is a full adder
+// over the row and its copies shifted by one cell, three such 2-bit numbers
+// are added by two more full adders, and the rule works on the carries as
+// they are: about 14 operations (two 3-input logic operations per full
+// adder) step 32 cells.
+//
+// Bound: HBM up to about 8 generations a pass, the VALU from about 16 on.
+// A region kept in LDS and read back for every generation (256-cell tiles in
+// 320-cell regions) took 288 us for 32 generations at n = 16384 and 60 us for
+// 17 at n = 3001; this form takes 122 and 10 us.  256-cell regions of 8 waves
+// and 4 rows per lane: 512-cell ones (77 % instead of 56 % of what is stepped
+// is kept at 32 generations) ran 142-166 us in five splits, their 700 to 1400
+// workgroups filling the chip unevenly; 8 rows per lane and 4 waves (fewer
+// operations per row) 140 against 138 us at the time.
 #pragma once
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "smap_ca2.hpp"
 #include "smap_decode.hpp"
 
 namespace smap {
-
-template <int RHO, int KH>
-struct Ca2kShape {
-    static constexpr int W = RHO + 2 * KH;   // cells per staged row (and rows)
-    static constexpr int DW = W / 32;         // dwords (32 cells) per staged row
-    static constexpr int NT = W <= 160 ? 64 : 256;   // threads
-    static constexpr int SEGS = NT / DW;      // row runs per dword column
-    static constexpr int RUN = (W + SEGS - 1) / SEGS;
-    static_assert(KH % 16 == 0 && RHO % 32 == 0 && W % 32 == 0 && DW <= NT, "bad CA2K shape");
-};
-
-// Simplex cells of the dword (x .. x+3, y): bytes kept.
-__device__ __forceinline__ uint32_t ca2k_keep_mask(int32_t x, int32_t y, int32_t n)
-{
-    if (x < 0 || y < 0) return 0u;
-    const int32_t keep = n - y - x + 1;
-    return keep >= 4 ? 0xFFFFFFFFu : (keep <= 0 ? 0u : (1u << (8 * keep)) - 1u);
-}
 
 // Simplex cells of the 32 cells x .. x+31 of row y, as bits (cells left of
 // the box, x < 0, and past the hypotenuse cleared).
@@ -59,6 +53,20 @@ __device__ __forceinline__ uint32_t ca2k_keep_bits(int32_t x, int32_t y, int32_t
     return m;
 }
 
+// The two parts of the same mask for a column of words: the cells x .. x+31
+// with x >= 0, and, given those, the cells of row y of which number `last`
+// (possibly negative or beyond 31) is the last inside.  Branch-free.
+__device__ __forceinline__ uint32_t ca2k_left_bits(int32_t x)
+{
+    return x <= -32 ? 0u : ~0u << (min(max(-x, 0), 31));
+}
+__device__ __forceinline__ uint32_t ca2k_row_bits(uint32_t left, int32_t last, int32_t y)
+{
+    const uint32_t past = 0xFFFFFFFEu << min(max(last, 0), 31);     // the cells after the last
+    const uint32_t none = (uint32_t)((last | y) >> 31);             // no cell at all
+    return left & ~past & ~none;
+}
+
 // Four 0/1 bytes -> 4 bits (byte k -> bit k): the product places byte k's
 // bit at bit 24 + k, every other partial product lands on a distinct bit
 // below 24 or beyond bit 31, so nothing carries into bits 24..27.
@@ -68,132 +76,197 @@ __device__ __forceinline__ uint32_t pack4(uint32_t d) { return ((d * 0x01020408u
 // lands on bit k + 7j, a multiple of 8 only for j = k, with no carries.
 __device__ __forceinline__ uint32_t unpack4(uint32_t v) { return ((v & 0xFu) * 0x00204081u) & 0x01010101u; }
 
-template <int RHO, int KH, bool SAFE>
+// Sixteen bytes -> 16 bits, bit k = bit 0 of byte k: dot products of the
+// 0/1 bytes with powers of two, eight bytes per accumulator.
+__device__ __forceinline__ uint32_t pack16(const uint4 &v)
+{
+    uint32_t lo = __builtin_amdgcn_udot4(v.x & 0x01010101u, 0x08040201u, 0u, false);
+    lo = __builtin_amdgcn_udot4(v.y & 0x01010101u, 0x80402010u, lo, false);
+    uint32_t hi = __builtin_amdgcn_udot4(v.z & 0x01010101u, 0x08040201u, 0u, false);
+    hi = __builtin_amdgcn_udot4(v.w & 0x01010101u, 0x80402010u, hi, false);
+    return lo | (hi << 8);
+}
+
+// One 3-input logic operation; the immediate is the function of the bit
+// patterns A, B, C (of the three inputs).
+constexpr uint32_t kBitA = 0xF0u, kBitB = 0xCCu, kBitC = 0xAAu;
+template <uint32_t F>
+__device__ __forceinline__ uint32_t bit3(uint32_t a, uint32_t b, uint32_t c)
+{
+    return __builtin_amdgcn_bitop3_b32(a, b, c, F & 0xFFu);
+}
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) { return bit3<kBitA ^ kBitB ^ kBitC>(a, b, c); }
+__device__ __forceinline__ uint32_t maj3(uint32_t a, uint32_t b, uint32_t c)
+{
+    return bit3<(kBitA & kBitB) | (kBitC & (kBitA ^ kBitB))>(a, b, c);
+}
+
+// B3/S23 on 32 cells: the horizontal 3-sums (lo, hi bits) of the rows above,
+// at and below them, and the cells themselves.  The 3x3 sum with the centre is
+// T = a + 2 (k + b) + 4 m; next = (T == 3) | (T == 4 & alive).
+__device__ __forceinline__ uint32_t life_bits(uint32_t p0, uint32_t p1, uint32_t c0, uint32_t c1, uint32_t n0,
+                                              uint32_t n1, uint32_t alive)
+{
+    const uint32_t a = xor3(p0, c0, n0), k = maj3(p0, c0, n0);
+    const uint32_t b = xor3(p1, c1, n1), m = maj3(p1, c1, n1);
+    const uint32_t t3 = bit3<(kBitA ^ kBitB) & ~kBitC>(k, b, m);                  // T - a == 2
+    const uint32_t t4 = bit3<~(kBitA ^ kBitB) & (kBitA ^ kBitC)>(k, b, m);        // T - a == 4
+    const uint32_t s = t4 & alive;
+    return bit3<(kBitA & kBitB) | (~kBitA & kBitC)>(a, t3, s);
+}
+
+// Generations of one pass at most.
+constexpr int kCa2kMaxGens = 32;
+
+// XL lanes of 32 cells side by side, R rows per lane, NW waves.
+template <int XL, int R, int NW>
+struct Ca2kShape {
+    static constexpr int W = 32 * XL;                // cells per region row; region rows
+    static constexpr int NG = (64 / XL) * NW;        // lane groups, one below the other
+    static constexpr int NT = 64 * NW;
+    static constexpr int RPI = NT / (2 * XL);        // rows the workgroup loads at once, 16 cells a lane
+    static constexpr int LB = W / RPI;               // pieces in flight per lane: the whole region
+    static_assert(64 % XL == 0 && NG * R == W && W % RPI == 0 && LB <= 8 && W > 2 * kCa2kMaxGens, "bad CA2K shape");
+};
+
+// Tile side that leaves a halo of at least `gens` cells in a region of W
+// cells: a multiple of 16, so that the tile is stored in whole 16-cell pieces.
+constexpr int ca2k_rho(int w, int gens) { return (w - 2 * gens) / 16 * 16; }
+
+template <int XL, int R, int NW, bool SAFE>
 __device__ __forceinline__ void ca2k_tile(const Plan &P, const uint8_t *__restrict__ in,
                                           uint8_t *__restrict__ out, const int32_t *t, int gens)
 {
-    using Sh = Ca2kShape<RHO, KH>;
-    constexpr int W = Sh::W, DW = Sh::DW, NT = Sh::NT, RUN = Sh::RUN;
-    __shared__ uint32_t buf[2][W][DW];
-    const int32_t n = P.n;
-    const int32_t x0 = t[0] * RHO, y0 = t[1] * RHO;
+    using Sh = Ca2kShape<XL, R, NW>;
+    constexpr int W = Sh::W, NG = Sh::NG, RPI = Sh::RPI, LB = Sh::LB;
+    __shared__ uint32_t stage[W][XL];               // the region as bits, while it is loaded and stored
+    __shared__ uint32_t edge[2][2][NG][XL];         // [generation parity][first row, last row][group][word]
+    const int32_t n = P.n, rho = P.rho;
+    const int32_t x0 = t[0] * rho, y0 = t[1] * rho;
     if (x0 + y0 > n) return;                    // uniform: BB tile outside the simplex
+    const int32_t halo = (W - rho) / 2;
     const int64_t pitch = P.stride[1];
     const int64_t total = pitch * pitch;
-    const int tid = threadIdx.x;
-    const int32_t xs = x0 - KH, ys = y0 - KH;   // cell of bit 0 of dword 0 of row 0
+    const int xl = threadIdx.x % XL, grp = threadIdx.x / XL;
+    const int32_t xs = x0 - halo, ys = y0 - halo;   // the region's first cell
+    const int32_t x = xs + 32 * xl, y = ys + grp * R;   // the lane's first cell
 
-    // 1. Stage the region: each dword is two 16-byte chunks, loaded from
-    //    their first cell (x >= 0 for every chunk with a simplex cell, KH
-    //    being a multiple of 16), cleared outside the simplex, packed to bits.
-    for (int q = tid; q < W * DW; q += NT) {
-        const int r = q / DW, c = q % DW;
-        const int32_t y = ys + r;
-        uint32_t word = 0u;
+    // 1. Load, 16 cells per lane: consecutive lanes take consecutive pieces of
+    //    a row, LB pieces per lane in flight.  A piece with no simplex cell
+    //    reads the buffer's first 16 bytes (from n = 15 on a 16-byte access
+    //    that starts at a simplex cell stays inside the buffer; below, the
+    //    byte-safe loads are used); one that starts left of the box is loaded
+    //    from x = 0 and its bits shifted.  The bits go through LDS to the lane
+    //    that owns their word.
+    {
+        const int32_t xc = xs + 16 * (int)(threadIdx.x % (2 * XL)), xa = max(xc, 0);
+        const int32_t rt = threadIdx.x / (2 * XL);
+        const uint32_t left = ca2k_left_bits(xc);
+        const uint32_t up16 = (uint32_t)min(max(-xc, 0), 31);
+        uint4 v[LB];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int32_t x = xs + 32 * c + 16 * h;
-            uint32_t w[4] = {0u, 0u, 0u, 0u};
-            const bool has = y >= 0 && y <= n && x >= 0 && x <= n - y;
+        for (int k = 0; k < LB; ++k) {
+            const int32_t yr = ys + k * RPI + rt;
+            const bool has = (yr >= 0) & (xc > -16) & (xa <= n - yr);
             if constexpr (SAFE) {
+                v[k] = make_uint4(0u, 0u, 0u, 0u);
                 if (has) {
-                    const int64_t rb = (int64_t)y * pitch;
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) w[i] = ld_masked(in + rb, x + 4 * i, y, n, total - rb);
+                    const int64_t rb = (int64_t)yr * pitch;
+                    v[k].x = ld_masked(in + rb, xa, yr, n, total - rb);
+                    v[k].y = ld_masked(in + rb, xa + 4, yr, n, total - rb);
+                    v[k].z = ld_masked(in + rb, xa + 8, yr, n, total - rb);
+                    v[k].w = ld_masked(in + rb, xa + 12, yr, n, total - rb);
                 }
             } else {
-                const uint4 v = *reinterpret_cast<const uint4 *>(has ? in + (int64_t)y * pitch + x : in);
-                w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) w[i] &= ca2k_keep_mask(x + 4 * i, y, n);
+                const int64_t at = (int64_t)yr * pitch + xa;
+                v[k] = *reinterpret_cast<const uint4 *>(in + (has ? at : 0));
             }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) word |= pack4(w[i]) << (16 * h + 4 * i);
         }
-        buf[0][r][c] = word;
+#pragma unroll
+        for (int k = 0; k < LB; ++k) {
+            const int r = k * RPI + rt;
+            const int32_t yr = ys + r;
+            const uint32_t w = (pack16(v[k]) << up16) & ca2k_row_bits(left, n - yr - xc, yr);
+            reinterpret_cast<uint16_t *>(&stage[r][0])[threadIdx.x % (2 * XL)] = (uint16_t)w;
+        }
     }
-    __syncthreads();
+    lds_barrier();
+    uint32_t a[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) a[r] = stage[grp * R + r][xl];
+    uint32_t keep[R];                               // the words' cells inside the simplex
+#pragma unroll
+    for (int r = 0; r < R; ++r) keep[r] = ca2k_row_bits(ca2k_left_bits(x), n - y - r - x, y + r);
 
-    // 2. `gens` generations, buffer g & 1 -> (g + 1) & 1.  Generation g
-    //    (0-based) only needs rows g+1 .. W-2-g (the cells nearer the
-    //    region's edge are already stale).  A workgroup whose whole region
-    //    lies inside the simplex skips the simplex mask.
-    const int col = tid % DW, seg = tid / DW;
-    const bool worker = tid < Sh::SEGS * DW;
-    const int r_a = seg * RUN, r_b = min(W, r_a + RUN);
-    const int32_t xcol = xs + 32 * col;
+    // 2. Generations.  A region that lies inside the simplex needs no mask.
     const bool interior = xs >= 0 && ys >= 0 && xs + ys + 2 * (W - 1) <= n;   // uniform
-    for (int g = 0; g < gens; ++g) {
-        const uint32_t(*src)[DW] = buf[g & 1];
-        uint32_t(*dst)[DW] = buf[(g + 1) & 1];
-        const int lo = max(r_a, g + 1), hi = min(r_b, W - 1 - g);
-        if (worker && lo < hi) {
-            // horizontal 3-sum of row r as two bit planes (s0: bit 0, s1: bit 1)
-            auto hrow = [&](int r, uint32_t &s0, uint32_t &s1, uint32_t &a) {
-                a = src[r][col];
-                const uint32_t l = col > 0 ? src[r][col - 1] : 0u;
-                const uint32_t rr = col + 1 < DW ? src[r][col + 1] : 0u;
-                const uint32_t L = __builtin_amdgcn_alignbit(a, l, 31);    // cell x-1
-                const uint32_t R = __builtin_amdgcn_alignbit(rr, a, 1);    // cell x+1
-                const uint32_t la = L ^ a;
-                s0 = la ^ R;
-                s1 = (L & a) | (R & la);
-            };
-            uint32_t p0, p1, c0, c1, n0, n1, pa, ca, na;
-            hrow(lo - 1, p0, p1, pa);
-            hrow(lo, c0, c1, ca);
-            for (int r = lo; r < hi; ++r) {
-                hrow(r + 1, n0, n1, na);
-                // T = p + c + n (three 2-bit numbers) as bits q3 q2 q1 q0
-                const uint32_t t0 = p0 ^ c0, k0 = p0 & c0;
-                const uint32_t x1 = p1 ^ c1;
-                const uint32_t t1 = x1 ^ k0, k1 = (p1 & c1) | (k0 & x1);
-                const uint32_t q0 = t0 ^ n0, m0 = t0 & n0;
-                const uint32_t y1 = t1 ^ n1;
-                const uint32_t q1 = y1 ^ m0, m1 = (t1 & n1) | (m0 & y1);
-                const uint32_t q2 = k1 ^ m1, q3 = k1 & m1;
-                // B3/S23 on the count with the centre: T == 3, or T == 4 and alive
-                uint32_t res = ~q3 & ((q0 & q1 & ~q2) | (ca & ~q0 & ~q1 & q2));
-                if (!interior) res &= ca2k_keep_bits(xcol, ys + r, n);
-                dst[r][col] = res;
+    auto hsum = [&](uint32_t c, uint32_t &s0, uint32_t &s1) {
+        const uint32_t l = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)c, 0x111, 0xf, 0xf, true);   // row_shr:1
+        const uint32_t r = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)c, 0x101, 0xf, 0xf, true);   // row_shl:1
+        const uint32_t L = __builtin_amdgcn_alignbit(c, l, 31);    // cell x-1
+        const uint32_t Rt = __builtin_amdgcn_alignbit(r, c, 1);    // cell x+1
+        s0 = xor3(L, c, Rt);
+        s1 = maj3(L, c, Rt);
+    };
+    const int up = max(grp - 1, 0), down = min(grp + 1, NG - 1);   // (the region's own edge rows go stale)
+    auto generations = [&](auto masked) {
+        for (int g = 0; g < gens; ++g) {
+            uint32_t(*e)[NG][XL] = edge[g & 1];
+            e[0][grp][xl] = a[0];
+            e[1][grp][xl] = a[R - 1];
+            lds_barrier();
+            const uint32_t above = e[1][up][xl], below = e[0][down][xl];
+            uint32_t p0, p1, c0, c1;
+            hsum(above, p0, p1);
+            hsum(a[0], c0, c1);
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                uint32_t n0, n1;
+                hsum(r + 1 < R ? a[r + 1] : below, n0, n1);
+                uint32_t res = life_bits(p0, p1, c0, c1, n0, n1, a[r]);
+                if constexpr (decltype(masked)::value) res &= keep[r];
+                a[r] = res;
                 p0 = c0; p1 = c1;
                 c0 = n0; c1 = n1;
-                ca = na;
             }
         }
-        __syncthreads();
-    }
+    };
+    if (interior) generations(std::false_type{});
+    else generations(std::true_type{});
 
-    // 3. Write the tile: 16 cells per lane-step, rho / 16 per tile row.
-    const uint32_t(*fin)[DW] = buf[gens & 1];
-    constexpr int LPR = RHO / 16;
-    for (int q = tid; q < RHO * LPR; q += NT) {
-        const int rr = q / LPR, lc = q % LPR;
-        const int32_t y = y0 + rr, x = x0 + 16 * lc;
-        const int32_t v = n - y - x + 1;
-        if (y > n || v <= 0) continue;
-        const int b = KH + 16 * lc;                   // region bit of the first cell
-        const uint32_t bits = fin[KH + rr][b / 32] >> (b % 32);
-        const uint32_t w0 = unpack4(bits), w1 = unpack4(bits >> 4), w2 = unpack4(bits >> 8),
-                       w3 = unpack4(bits >> 12);
-        uint8_t *row = out + (int64_t)y * pitch;
+    // 3. Store, again 16 cells per lane with consecutive lanes along a row;
+    //    the tile starts `halo` bits into the region.
+#pragma unroll
+    for (int r = 0; r < R; ++r) stage[grp * R + r][xl] = a[r];
+    lds_barrier();
+    const int bit = halo + 16 * (int)(threadIdx.x % (2 * XL));   // region bit of the lane's first cell
+    const int32_t xo = x0 + bit - halo;
+    if (bit + 16 > halo + rho) return;
+    const int wd = bit >> 5, sh = bit & 31;
+    const int wn = min(wd + 1, XL - 1);               // (unused where the piece lies in one word)
+#pragma unroll 2
+    for (int r = threadIdx.x / (2 * XL); r < rho; r += RPI) {
+        const int32_t yr = y0 + r;
+        const int32_t v = n - yr - xo + 1;           // simplex cells from xo on
+        if (v <= 0) break;
+        const uint32_t w = __builtin_amdgcn_alignbit(stage[halo + r][wn], stage[halo + r][wd], sh);
+        uint32_t w4[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) w4[i] = unpack4(w >> (4 * i));
+        uint8_t *row = out + (int64_t)yr * pitch;
         if (v >= 16) {
-            *reinterpret_cast<uint4 *>(row + x) = make_uint4(w0, w1, w2, w3);
+            *reinterpret_cast<uint4 *>(row + xo) = make_uint4(w4[0], w4[1], w4[2], w4[3]);
         } else {
-            st_masked(row, x, y, n, w0);
-            st_masked(row, x + 4, y, n, w1);
-            st_masked(row, x + 8, y, n, w2);
-            st_masked(row, x + 12, y, n, w3);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) st_masked(row, xo + 4 * i, yr, n, w4[i]);
         }
     }
 }
 
-// (the launch bound is Ca2kShape<RHO, KH>::NT, written without commas)
-template <int RHO, int KH, bool BB, bool SAFE>
-__global__ __launch_bounds__(RHO + 2 * KH <= 160 ? 64 : 256) void k_ca2k(const Plan P, const uint8_t *__restrict__ in,
-                                                                        uint8_t *__restrict__ out, int gens)
+template <int XL, int R, int NW, bool BB, bool SAFE>
+__global__ __launch_bounds__(64 * NW, 8) void k_ca2k(const Plan P, const uint8_t *__restrict__ in,
+                                                     uint8_t *__restrict__ out, int gens)
 {
-    static_assert(Ca2kShape<RHO, KH>::NT == (RHO + 2 * KH <= 160 ? 64 : 256), "launch bound");
     int32_t t[4] = {0, 0, 0, 0};
     const WgId g = wg_id(P);
     if (BB) {
@@ -201,7 +274,7 @@ __global__ __launch_bounds__(RHO + 2 * KH <= 160 ? 64 : 256) void k_ca2k(const P
     } else {
         if (!decode_h<2>(P, g.x, t)) return;
     }
-    ca2k_tile<RHO, KH, SAFE>(P, in, out, t, gens);
+    ca2k_tile<XL, R, NW, SAFE>(P, in, out, t, gens);
 }
 
 }  // namespace smap

@@ -1313,10 +1313,34 @@ int graph_create(int m, int64_t n, int r, int beta, int op, bool bb, const void 
     return kOk;
 }
 
-// ---- several generations per pass (CA2) ------------------------------------
+// ---- several generations per pass -------------------------------------------
 
-constexpr int kStepsRho = 256, kStepsKh = 32;   // tile side and halo (= generations per pass)
-constexpr TileCfg kStepsTile = {kStepsRho, Ca2kShape<kStepsRho, kStepsKh>::NT, 1};
+// CA2: the region of a workgroup is W x W cells (Ca2kShape), its tile what is
+// left inside a halo of the pass's generations.
+template <int XL, int R, int NW, bool SAFE>
+void launch_ca2k(bool bb, const Plan &P, dim3 grid, const uint8_t *in, uint8_t *out, int gens, hipStream_t s)
+{
+    constexpr int NT = Ca2kShape<XL, R, NW>::NT;
+    if (bb)
+        hipLaunchKernelGGL((k_ca2k<XL, R, NW, true, SAFE>), grid, dim3(NT), 0, s, P, in, out, gens);
+    else
+        hipLaunchKernelGGL((k_ca2k<XL, R, NW, false, SAFE>), grid, dim3(NT), 0, s, P, in, out, gens);
+}
+
+// Region width of a pass of `gens` generations over Delta_n^2: 256 cells, or
+// 128 where a pass of 128-cell regions is short.  A small region keeps little
+// of what it steps (128 - 2 gens cells of 128 a side) but a generation of it
+// takes a quarter of the time, and a board of few tiles is bound by that time:
+// a workgroup's own chain of generations.  Measured (us; 128, 256): n = 1000,
+// 17 generations 9.6, 14.8; n = 3001, 17: 11.2, 15.0 (722 tiles of 80 cells);
+// n = 5000, 17: 21.1, 22.8 (1984); n = 3001, 32: 22.8, 21.6 (1104 of 64);
+// n = 8191, 8: 17.5, 19.4 (2738 of 112); n = 8191, 17: 42.5, 33.5 (5253).
+int steps2_region(int64_t n, int gens)
+{
+    const int64_t k = n / ca2k_rho(128, gens) + 1;
+    return k * (k + 1) / 2 * (gens + 8) <= 48000 ? 128 : 256;
+}
+
 // CA3: 64^3 tiles, 16-cell halo (16 generations per pass), one bit per cell
 constexpr int kSteps3Rho = 64, kSteps3Kh = 16;
 constexpr TileCfg kSteps3Tile = {kSteps3Rho, Ca3kShape<kSteps3Rho, kSteps3Kh>::NT, 1};
@@ -1336,10 +1360,18 @@ int steps_launch(int m, int64_t n, int r, int beta, int op, int32_t steps, void 
     }
     rc = check_buffers(m, n, op, a, b);
     if (rc != kOk) return rc;
+    // passes of at most kh generations, alternating a -> b -> a ...;
+    // an odd number of passes, so that the last one writes b
+    const int kh = ca3 ? kSteps3Kh : kCa2kMaxGens;
+    int passes = (steps + kh - 1) / kh;
+    if (passes % 2 == 0) ++passes;
+    const int gmax = (steps + passes - 1) / passes;   // generations of the longest pass
+    const int w2 = ca3 ? 0 : steps2_region(n, gmax);
     Plan P;
     {
         std::lock_guard<std::mutex> lk(g_mu);
-        rc = plan_for(m, n, bt, bb, ca3 ? 2 : 1, ca3 ? kSteps3Tile : kStepsTile, &P, nullptr, true);
+        rc = plan_for(m, n, bt, bb, ca3 ? 2 : 1, ca3 ? kSteps3Tile : TileCfg{ca2k_rho(w2, gmax), 0, 1}, &P, nullptr,
+                      true);
     }
     if (rc != kOk) return rc;
     if (P.total == 0) return kOk;
@@ -1352,20 +1384,14 @@ int steps_launch(int m, int64_t n, int r, int beta, int op, int32_t steps, void 
     P.grid_div[0] = make_divu(grid.x);
     P.grid_div[1] = make_divu(grid.y);
     P.remap = bb ? 2u : 1u;
-    // passes of at most kStepsKh generations, alternating a -> b -> a ...;
-    // an odd number of passes, so that the last one writes b
-    const int kh = ca3 ? kSteps3Kh : kStepsKh;   // generations per pass at most
-    int passes = (steps + kh - 1) / kh;
-    if (passes % 2 == 0) ++passes;
     hipStream_t s = (hipStream_t)stream;
     int left = steps;
     for (int i = 0; i < passes; ++i) {
-        const int g = (left + (passes - i) - 1) / (passes - i);   // spread evenly, 1..kh
+        const int g = (left + (passes - i) - 1) / (passes - i);   // spread evenly, 1..gmax
         const uint8_t *src = (const uint8_t *)((i & 1) ? b : a);
         uint8_t *dst = (uint8_t *)((i & 1) ? a : b);
         const bool safe = n < 15;
         constexpr int nt3 = Ca3kShape<kSteps3Rho, kSteps3Kh>::NT;
-        constexpr int nt2 = Ca2kShape<kStepsRho, kStepsKh>::NT;
         if (ca3) {
             if (bb) {
                 if (safe) hipLaunchKernelGGL((k_ca3k<kSteps3Rho, kSteps3Kh, true, true>), grid, dim3(nt3), 0, s, P, src, dst, g);
@@ -1374,12 +1400,12 @@ int steps_launch(int m, int64_t n, int r, int beta, int op, int32_t steps, void 
                 if (safe) hipLaunchKernelGGL((k_ca3k<kSteps3Rho, kSteps3Kh, false, true>), grid, dim3(nt3), 0, s, P, src, dst, g);
                 else hipLaunchKernelGGL((k_ca3k<kSteps3Rho, kSteps3Kh, false, false>), grid, dim3(nt3), 0, s, P, src, dst, g);
             }
-        } else if (bb) {
-            if (safe) hipLaunchKernelGGL((k_ca2k<kStepsRho, kStepsKh, true, true>), grid, dim3(nt2), 0, s, P, src, dst, g);
-            else hipLaunchKernelGGL((k_ca2k<kStepsRho, kStepsKh, true, false>), grid, dim3(nt2), 0, s, P, src, dst, g);
+        } else if (safe) {   // (a small board: 128-cell regions)
+            launch_ca2k<4, 2, 4, true>(bb, P, grid, src, dst, g, s);
+        } else if (w2 == 128) {
+            launch_ca2k<4, 2, 4, false>(bb, P, grid, src, dst, g, s);
         } else {
-            if (safe) hipLaunchKernelGGL((k_ca2k<kStepsRho, kStepsKh, false, true>), grid, dim3(nt2), 0, s, P, src, dst, g);
-            else hipLaunchKernelGGL((k_ca2k<kStepsRho, kStepsKh, false, false>), grid, dim3(nt2), 0, s, P, src, dst, g);
+            launch_ca2k<8, 4, 8, false>(bb, P, grid, src, dst, g, s);
         }
         if (hipGetLastError() != hipSuccess) return kEhip;
         left -= g;

@@ -87,6 +87,30 @@ def test_steps_workload_size_matches_single_steps(smap):
     assert torch.equal(a, orig)             # one pass leaves the input untouched
 
 
+@pytest.mark.parametrize("kind", ["h", "bb"])
+@pytest.mark.parametrize("n,steps", [
+    # 256-cell regions: tiles of 192 cells (32 and 31 generations), sizes at
+    # and one either side of a tile's edge; 208 (23); 240 (2)
+    (3455, 32), (3456, 32), (3457, 31), (5200, 23), (10000, 2),
+    # 128-cell regions at their largest boards: tiles of 64, 80 and 112 cells
+    (2999, 32), (4799, 24), (7503, 5)])
+def test_steps_region_widths(smap, kind, n, steps):
+    """Both region widths of the 2-D pass against single-step launches."""
+    a = si.box_torch(2, n, "bern", 8200 + n, p=0.35, device="cuda")
+    x, y = a.clone(), a.clone()
+    for _ in range(steps):
+        smap.map_launch(2, n, "ca2", x, y)
+        x, y = y, x
+    out = si.sentinel_box_torch(2, n, True, device="cuda")
+    say(f"{kind} n={n} steps={steps}")
+    (smap.map_launch_steps if kind == "h" else smap.bb_launch_steps)(2, n, "ca2", steps, a, out)
+    torch.cuda.synchronize()
+    r = torch.arange(n + 1, device="cuda")
+    inside = (r.view(-1, 1) + r.view(1, -1)) <= n
+    assert torch.equal(out[inside], x[inside])
+    assert bool((out[~inside] == si.SENTINEL_U8).all())
+
+
 SIZES3 = [0, 1, 5, 14, 15, 16, 31, 32, 33, 40, 63, 64, 65, 100, 130]
 STEPS3 = [1, 2, 3, 5, 9, 16, 17, 33]
 
