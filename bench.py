@@ -580,7 +580,7 @@ def main():
         "data": "synthetic (seeded splitmix64)",
         "config": {"workload": f"{args.workload}: m={m} n={n} op={op}", "m": m, "n": n,
                    "op": op, "useful_elements": useful,
-                   "rho": info_h["rho"] if args.gens == 0 else (256 if m == 2 else 64),
+                   "rho": info_h["rho"] if args.gens == 0 else None,
                    "beta": info_h["beta"], "autotuned": tuned, "graph_launches": args.graph or None,
                    "generations_per_call": gens, "layout3": args.layout3 if m == 3 else None,
                    "general": args.general,
@@ -606,9 +606,7 @@ def main():
             "unit": "GB/s",
             "frac": achieved / PEAK_HBM_GBS,
             "traffic": traffic,
-            "kernel": f"{op} H launch" + (f" ({gens} generations per call, "
-                                          + ("rho 256, halo 32)" if m == 2 else "rho 64, halo 16)")
-                                          if args.gens else ""),
+            "kernel": f"{op} H launch" + (f" ({gens} generations per call)" if args.gens else ""),
             "kernel_sha": kernel_sha(op),
             "bytes_per_launch": alg_bytes,
             "copy_gbs": None if copy is None else copy["gbs"],

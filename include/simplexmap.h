@@ -202,8 +202,9 @@ int simplex_set_shape(int m, int op, int rho, int wg_threads, int tiles_per_wg);
 /*
  * Layout of the native part of the 3-D H map for later launches of this
  * process (H launches, plans and plan info; BB is not affected):
- *   SMAP_LAYOUT_AUTO (default): LEVELS for one-job CA3 launches (one step
- *     or several generations, their plans and plan info), PACKED for the
+ *   SMAP_LAYOUT_AUTO (default): LEVELS for one-job CA3 launches of one
+ *     step (their plans and plan info; passes of several generations map
+ *     columns and have no 3-D native part), PACKED for the
  *     per-element ops and for the batched and work-queue launches;
  *   SMAP_LAYOUT_PACKED: the packed grid (N/2) x (N/2) x (N/2 + N/4)
  *     of Section 4.3, one launch, 1/8 of its workgroups discarded
@@ -330,7 +331,9 @@ int simplex_copy_launch(int m, int64_t n, const void *buf_in, void *buf_out, voi
  *   m = 2, SMAP_OP_CA2: tiles of 64 to 240 cells a side inside regions of
  *     128 or 256 cells, chosen from n and the generations of a pass: up to
  *     G = 32 per pass;
- *   m = 3, SMAP_OP_CA3: 64^3 tiles, halo 16: up to G = 16 per pass.
+ *   m = 3, SMAP_OP_CA3: columns of 32 to 112 cells a side inside regions of
+ *     64 or 128, found with the 2-D map, whose planes stream through the
+ *     chip in pieces: up to G = 16 per pass.
  *
  * buf_out receives the state after `steps` generations of buf_in (layout
  * and rules as for simplex_map_launch; the buffers must not overlap).

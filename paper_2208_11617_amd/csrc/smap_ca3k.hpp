@@ -2,29 +2,40 @@
 //
 // The paper's automaton test runs a fixed number of steps (Section 5.1);
 // this is that loop on the 3-simplex, blocked in time.  One launch advances
-// every cell of Delta_n^3 by `gens` <= KH generations: a workgroup loads its
-// rho^3 tile plus a halo of KH cells on every side into LDS (cells outside
-// the simplex, or outside the box, dead), steps the region `gens` times in
-// LDS and writes the tile.  After generation g the cells within g of the
-// region's faces are stale, so with gens <= KH the tile itself is exact.
-// HBM bytes per generation: ((rho + 2 KH)^3 / rho^3 + 1) / gens per cell
-// instead of 2.
+// every cell of Delta_n^3 by `gens` <= 16 generations.  The (x_1, x_2) plane
+// is cut into tiles of rho x rho cells, those that meet the 2-simplex being
+// the columns of the 3-simplex; a column's planes are cut into pieces of about
+// the same height, one workgroup each, which reads its piece with a halo of
+// `gens` planes and (W - rho) / 2 >= gens cells on each side (cells outside
+// the simplex, or outside the box, dead).  H finds the columns with the 2-D
+// map (Theorem 1); the host lists the pieces, tallest first, in the kernel's
+// arguments, so that a launch is a whole number of rounds over the chip.
 //
-// In LDS a cell is one bit: ONE buffer of W = rho + 2 KH planes x W rows x
-// W/32 dwords (110,592 bytes for rho = 64, KH = 16); bit b of dword c of row
-// y of plane z is the cell (x0 - KH + 32c + b, y0 - KH + y, z0 - KH + z).
-// The count is bit-sliced, 32 cells per operation: a row's horizontal
-// 3-sum is a full adder over the row and its copies shifted by one cell
-// (2 bits per cell), the in-plane 3x3 sum adds three of those (4 bits, at
-// most 9), and the 3x3x3 sum including the centre adds three in-plane sums
-// (5 bits, at most 27).  A generation updates the region in place: a thread
-// owns one dword of one row and walks the planes along z with the in-plane
-// sums of the two previous planes in registers; the new plane z is written
-// one step later, once every thread has read the old plane z, so threads
-// up to one step apart never touch a plane another reads or writes (one
-// barrier per two planes).  Three parts of the workgroup walk three ranges
-// of the planes at once.  Generation g updates planes and rows g .. W-1-g
-// only.
+// The planes stream through the workgroup along z, all generations at
+// once: at step s generation g turns plane s - 2g of generation g - 1 into its
+// own, from that plane, the one below and the one above, which generation
+// g - 1 made in the step before.  So the generations of a step do not depend on
+// each other, every WPG waves of the workgroup work on one of them, and a
+// step needs one barrier.  A generation hands its plane to the next through
+// LDS (two planes of W x W bits each); what it needs of the planes below are
+// their in-plane 3x3 sums, which stay in registers.  Loading a plane (16
+// cells per lane, a step or two ahead) and storing the finished one are spread
+// over all threads.
+//
+// A cell is one bit: a lane holds a column of R words (32 cells along x), XW
+// lanes side by side, a generation's lanes covering the W x W plane.  The
+// count is bit-sliced, in three-input logic operations: a row's 3-sum is a
+// full adder over the row and its copies shifted by one cell (the
+// neighbouring words by DPP), three rows are added by one full adder per bit
+// and kept as the four bits q + 2 (k + t) + 4 m, and three planes of those
+// are added by eight more.  Each generation the outermost cells of the
+// region go stale by one; the tile itself never sees them.
+//
+// Bound: the VALU at 16 generations (41 operations per 32 cells), HBM and the
+// load latency at 2.  n = 1024, 16 generations: 336 us (the form before, whole
+// 96^3 regions in LDS stepped one generation after another with one
+// workgroup a CU: 1409); n = 301, 8: 26 us (215, 35 workgroups).  A 128 x 128
+// plane and 16 waves are what the registers of a CU hold the sums of.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -36,243 +47,243 @@
 
 namespace smap {
 
-template <int RHO, int KH>
+// Generations of one pass at most.
+constexpr int kCa3kMaxGens = 16;
+
+// XW words (32 cells) and 32 XW rows a plane, R rows per lane, WPG waves per
+// generation.
+template <int XW, int R, int WPG>
 struct Ca3kShape {
-    static constexpr int W = RHO + 2 * KH;        // cells per staged row; rows; planes
-    static constexpr int DW = W / 32;              // dwords (32 cells) per staged row
-    static constexpr int NCOL = DW * (W - 2);      // thread columns: a dword of rows 1 .. W-2
-    static constexpr int NP = 3;                   // parts of the plane walk, walked at once
-    static constexpr int PART = ((NCOL + 63) / 64) * 64;   // threads per part
-    static constexpr int NT = NP * PART;
-    static_assert(W % 32 == 0 && KH % 16 == 0 && RHO % 32 == 0 && NT <= 1024, "bad CA3K shape");
+    static constexpr int W = 32 * XW;
+    static constexpr int YG = 64 * WPG / XW;          // lane rows of a generation
+    static constexpr int GS = 16 / WPG;               // generations the workgroup holds
+    static constexpr int CH = W * 2 * XW;             // 16-cell pieces of a plane
+    // LDS words of one lane row: a stride that spreads the lane rows' reads over all banks
+    static constexpr int GP = R * XW + (R * XW % (2 * XW) == 0 ? XW : 0);
+    static constexpr int PL = YG * GP;                // LDS words of a plane
+    static_assert(YG * R == W && 64 * WPG % XW == 0 && CH <= 1024 && (XW == 2 || XW == 4), "bad CA3K shape");
+    static constexpr int threads(int gens)            // of a pass of `gens` generations
+    {
+        return 64 * WPG * gens > CH ? 64 * WPG * gens : CH;
+    }
 };
 
-// Simplex cells of the dword (x .. x+3, y, z): bytes kept.
-__device__ __forceinline__ uint32_t ca3k_keep_mask(int32_t x, int32_t y, int32_t z, int32_t n)
+// Pieces of one H launch: x tile, y tile (10 bits each) and piece (12 bits).
+constexpr int kCa3kUnits = 768;
+struct Ca3kUnits {
+    uint32_t unit[kCa3kUnits];
+};
+
+constexpr int ca3k_rho(int w, int gens) { return (w - 2 * gens) / 16 * 16; }
+
+// In-plane 3x3 sum q + 2 (k + t) + 4 m of 32 cells.
+struct Ca3kSum {
+    uint32_t q, k, t, m;
+};
+
+// B6/S567 from three planes' sums and the cells themselves (which are dead
+// outside `left`); the result's bits outside `left` and `keep` are cleared.
+__device__ __forceinline__ uint32_t ca3k_rule(const Ca3kSum &a, const Ca3kSum &b, const Ca3kSum &c, uint32_t alive,
+                                              uint32_t left, uint32_t keep)
 {
-    if (x < 0 || y < 0 || z < 0) return 0u;
-    const int32_t keep = n - z - y - x + 1;
-    return keep >= 4 ? 0xFFFFFFFFu : (keep <= 0 ? 0u : (1u << (8 * keep)) - 1u);
+    // T = t0 + 2 t1 + 4 t2 + 8 t3 + 16 t4 (at most 27, the centre included)
+    const uint32_t t0 = xor3(a.q, b.q, c.q), u = maj3(a.q, b.q, c.q);
+    const uint32_t k = xor3(a.k, b.k, c.k), ck = maj3(a.k, b.k, c.k);
+    const uint32_t t = xor3(a.t, b.t, c.t), ct = maj3(a.t, b.t, c.t);
+    const uint32_t t1 = xor3(u, k, t), cu = maj3(u, k, t);
+    const uint32_t m = xor3(a.m, b.m, c.m), cm = maj3(a.m, b.m, c.m);
+    const uint32_t v = xor3(ck, ct, cu), cv = maj3(ck, ct, cu);
+    const uint32_t t2 = m ^ v, cw = m & v;
+    const uint32_t t3 = xor3(cm, cv, cw), t4 = maj3(cm, cv, cw);
+    const uint32_t e67 = bit3<kBitA & kBitB & ~kBitC>(t1, t2, t3);          // T = 6 or 7 (mod 16)
+    const uint32_t e89 = bit3<~kBitA & ~kBitB & kBitC>(t1, t2, t3);         // T = 8 or 9
+    const uint32_t born = bit3<kBitA & ~kBitB & kBitC>(e67, t0, left);      // T = 6
+    const uint32_t stay = bit3<kBitA | (kBitB & ~kBitC)>(e67, e89, t0);     // T = 6, 7 or 8
+    const uint32_t next = bit3<(kBitA & kBitB) | (~kBitA & kBitC)>(alive, stay, born);
+    return bit3<kBitA & ~kBitB & kBitC>(next, t4, keep);
 }
 
-// Sum of three 2-bit bit-sliced numbers (a1 a0) + (b1 b0) + (c1 c0): 4 bits.
-__device__ __forceinline__ void add3_2(uint32_t a0, uint32_t a1, uint32_t b0, uint32_t b1, uint32_t c0, uint32_t c1,
-                                       uint32_t (&q)[4])
+template <int XW, int R, int WPG, bool SAFE>
+__device__ __forceinline__ void ca3k_tile(const Plan &P, const uint8_t *__restrict__ in, uint8_t *__restrict__ out,
+                                          int32_t tx, int32_t ty, int32_t sub, int gens, int rz)
 {
-    const uint32_t t0 = a0 ^ b0, k0 = a0 & b0;
-    const uint32_t x1 = a1 ^ b1;
-    const uint32_t t1 = x1 ^ k0, k1 = (a1 & b1) | (k0 & x1);
-    q[0] = t0 ^ c0;
-    const uint32_t m0 = t0 & c0;
-    const uint32_t y1 = t1 ^ c1;
-    q[1] = y1 ^ m0;
-    const uint32_t m1 = (t1 & c1) | (m0 & y1);
-    q[2] = k1 ^ m1;
-    q[3] = k1 & m1;
-}
-
-template <int RHO, int KH, bool SAFE>
-__device__ __forceinline__ void ca3k_tile(const Plan &P, const uint8_t *__restrict__ in,
-                                          uint8_t *__restrict__ out, const int32_t *t, int gens)
-{
-    using Sh = Ca3kShape<RHO, KH>;
-    constexpr int W = Sh::W, DW = Sh::DW, NT = Sh::NT;
-    __shared__ uint32_t buf[W][W][DW];
-    const int32_t n = P.n;
-    const int32_t x0 = t[0] * RHO, y0 = t[1] * RHO, z0 = t[2] * RHO;
-    if (x0 + y0 + z0 > n) return;                // uniform: BB tile outside the simplex
-    const int64_t p1 = P.stride[1], p2 = P.stride[2];
+    using Sh = Ca3kShape<XW, R, WPG>;
+    constexpr int W = Sh::W, GP = Sh::GP, PL = Sh::PL, YG = Sh::YG;
+    __shared__ uint32_t buf[2][Sh::GS + 1][PL];       // [step parity][generation][plane]
+    const int32_t n = P.n, rho = P.rho;
+    const int32_t x0 = tx * rho, y0 = ty * rho, height = n - x0 - y0 + 1;
+    if (sub * rz >= height) return;                    // uniform: BB piece outside the simplex
+    // the column's planes in pieces of at most rz, as even as they come
+    const int32_t pieces = (height + rz - 1) / rz, each = (height + pieces - 1) / pieces;
+    const int32_t z0 = sub * each, z1 = min(z0 + each, height) - 1;
+    if (z0 > z1) return;
+    const int32_t halo = (W - rho) / 2;
+    const int32_t xs = x0 - halo, ys = y0 - halo;     // the region's first cell
+    // the first plane with no live cell in the region: its mask is empty, so
+    // what it is made from does not matter, and none above it is made
+    const int32_t ztop = n - max(xs, 0) - max(ys, 0) + 1;
+    const int64_t p1 = n + 1, p2 = p1 * p1;
     const int64_t total = p2 * p1;
     const int tid = threadIdx.x;
-    const int32_t xs = x0 - KH, ys = y0 - KH, zs = z0 - KH;   // cell of bit 0, dword 0, row 0, plane 0
+    const int gen = __builtin_amdgcn_readfirstlane(tid / (64 * WPG)) + 1;   // the wave's generation
 
-    // 1. Stage the region.  A dword is two 16-byte chunks, each loaded from
-    //    its first cell (x >= 0 for every chunk with a simplex cell, KH being
-    //    a multiple of 16), cleared outside the simplex and packed to bits.
-    //    From n = 15 on a 16-byte access from a simplex cell stays inside the
-    //    buffer, so LB dwords' loads are issued unconditionally (the buffer's
-    //    first 16 bytes for a chunk without a simplex cell) before any is
-    //    used; below, bytes go through the masked load.
-    constexpr int NL = W * W * DW, LB = 4;
-    uint32_t *flat = &buf[0][0][0];
-    for (int q0 = tid; q0 < NL; q0 += NT * LB) {
-        uint4 v[LB][2];
-        int32_t cx[LB], cy[LB], cz[LB];
-#pragma unroll
-        for (int k = 0; k < LB; ++k) {
-            const int q = min(q0 + k * NT, NL - 1);
-            const int c = q % DW, y = (q / DW) % W, z = q / (DW * W);
-            cx[k] = xs + 32 * c;
-            cy[k] = ys + y;
-            cz[k] = zs + z;
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int32_t x = cx[k] + 16 * h;
-                const bool has = cy[k] >= 0 && cz[k] >= 0 && x >= 0 && x <= n - cy[k] - cz[k];
-                if constexpr (SAFE) {
-                    v[k][h] = make_uint4(0u, 0u, 0u, 0u);
-                    if (has) {
-                        const int64_t rb = (int64_t)cz[k] * p2 + (int64_t)cy[k] * p1;
-                        const int32_t r = cy[k] + cz[k];
-                        v[k][h].x = ld_masked(in + rb, x, r, n, total - rb);
-                        v[k][h].y = ld_masked(in + rb, x + 4, r, n, total - rb);
-                        v[k][h].z = ld_masked(in + rb, x + 8, r, n, total - rb);
-                        v[k][h].w = ld_masked(in + rb, x + 12, r, n, total - rb);
-                    }
-                } else {
-                    const uint8_t *a = has ? in + ((int64_t)cz[k] * p2 + (int64_t)cy[k] * p1 + x) : in;
-                    v[k][h] = *reinterpret_cast<const uint4 *>(a);
-                }
+    // Loading: the thread's 16-cell piece of every plane.  A piece with no
+    // simplex cell reads the buffer's first 16 bytes (from n = 15 on a 16-byte
+    // access that starts at a simplex cell stays inside the buffer; below, the
+    // byte-safe loads are used); one that starts left of the box is loaded
+    // from x = 0 and its bits shifted.
+    const int lr = tid / (2 * XW), lc = tid % (2 * XW);
+    const int32_t ly = ys + lr, lx = xs + 16 * lc, lxa = max(lx, 0);
+    const bool loads = tid < Sh::CH;
+    const int32_t lz = loads && ly >= 0 && lx > -16 ? n - ly - lxa : -1;    // planes 0 .. lz hold a cell of the piece
+    const uint32_t loff = (uint32_t)max(ly, 0) * (uint32_t)p1 + (uint32_t)lxa;
+    const uint32_t lleft = ca2k_left_bits(lx), lup = (uint32_t)min(max(-lx, 0), 31);
+    auto load = [&](int32_t z) {
+        uint4 v = make_uint4(0u, 0u, 0u, 0u);
+        const bool has = z <= lz;
+        if constexpr (SAFE) {
+            if (has) {
+                const int64_t rb = (int64_t)z * p2 + (int64_t)ly * p1;
+                v.x = ld_masked(in + rb, lxa, ly + z, n, total - rb);
+                v.y = ld_masked(in + rb, lxa + 4, ly + z, n, total - rb);
+                v.z = ld_masked(in + rb, lxa + 8, ly + z, n, total - rb);
+                v.w = ld_masked(in + rb, lxa + 12, ly + z, n, total - rb);
             }
-        }
-#pragma unroll
-        for (int k = 0; k < LB; ++k) {
-            uint32_t word = 0u;
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int32_t x = cx[k] + 16 * h;
-                const uint32_t w[4] = {v[k][h].x, v[k][h].y, v[k][h].z, v[k][h].w};
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    word |= pack4(w[i] & ca3k_keep_mask(x + 4 * i, cy[k], cz[k], n)) << (16 * h + 4 * i);
-            }
-            if (q0 + k * NT < NL) flat[q0 + k * NT] = word;
-        }
-    }
-    __syncthreads();
-
-    // 2. Generations.  Thread column: dword c of row y.  The planes of a
-    //    generation are cut into NP consecutive ranges, walked by NP parts of
-    //    the workgroup at once.  A part keeps its first new plane in a
-    //    register until the generation ends (the part below reads that
-    //    plane's old cells at its last step), and every part writes its last
-    //    new plane only then (the part above read it at its first step).
-    const int part = tid / Sh::PART, lt = tid % Sh::PART;
-    const bool worker = lt < Sh::NCOL;
-    const int c = lt % DW;
-    const int y = 1 + lt / DW;
-    const int32_t gx = xs + 32 * c;
-    const bool interior = xs >= 0 && ys >= 0 && zs >= 0 && xs + ys + zs + 3 * (W - 1) <= n;   // uniform
-    // in-plane 3x3 sum of the thread's cells in plane z (4 bits) and the centres
-    auto plane_sum = [&](int z, uint32_t (&S)[4], uint32_t &C) {
-        uint32_t s0[3], s1[3];
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            const uint32_t *row = buf[z][y - 1 + j];
-            const uint32_t a = row[c];
-            const uint32_t l = c > 0 ? row[c - 1] : 0u;
-            const uint32_t r = c + 1 < DW ? row[c + 1] : 0u;
-            const uint32_t L = __builtin_amdgcn_alignbit(a, l, 31);    // cell x-1
-            const uint32_t R = __builtin_amdgcn_alignbit(r, a, 1);     // cell x+1
-            const uint32_t la = L ^ a;
-            s0[j] = la ^ R;
-            s1[j] = (L & a) | (R & la);
-            if (j == 1) C = a;
-        }
-        add3_2(s0[0], s1[0], s0[1], s1[1], s0[2], s1[2], S);
-    };
-    for (int g = 1; g <= gens; ++g) {
-        const int z_lo = g, z_hi = W - 1 - g;     // planes (and rows) updated by this generation
-        const int steps = (z_hi - z_lo + Sh::NP) / Sh::NP;   // planes per part (uniform)
-        const int za = z_lo + part * steps, zb = min(z_hi, za + steps - 1);   // this part's planes
-        const bool active = worker && y >= g && y <= W - 1 - g;
-        uint32_t Sp[4], Sc[4], Cc = 0u, Cp = 0u, pend = 0u, first = 0u;
-        if (active) {
-            plane_sum(za - 1, Sp, Cp);
-            plane_sum(za, Sc, Cc);
-        }
-        __syncthreads();   // plane za is read here and rewritten at step za + 1
-        for (int i = 0; i < steps; ++i) {
-            const int z = za + i;
-            if (active && z <= zb) {
-                uint32_t Sn[4], Cn;
-                plane_sum(z + 1, Sn, Cn);
-                if (z > za) {
-                    if (part > 0 && z == za + 1) first = pend;   // written at the end
-                    else buf[z - 1][y][c] = pend;
-                }
-                // U = Sp + Sc (5 bits), T = U + Sn (5 bits, at most 27)
-                uint32_t u[5], tt[5], cr = 0u;
-#pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    const uint32_t x1 = Sp[b] ^ Sc[b];
-                    u[b] = x1 ^ cr;
-                    cr = (Sp[b] & Sc[b]) | (cr & x1);
-                }
-                u[4] = cr;
-                cr = 0u;
-#pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    const uint32_t x1 = u[b] ^ Sn[b];
-                    tt[b] = x1 ^ cr;
-                    cr = (u[b] & Sn[b]) | (cr & x1);
-                }
-                tt[4] = u[4] ^ cr;
-                // B6/S567 on the count with the centre: T == 6, or T in {7, 8} and alive
-                const uint32_t e67 = ~tt[4] & ~tt[3] & tt[2] & tt[1];
-                const uint32_t e8 = ~tt[4] & tt[3] & ~tt[2] & ~tt[1] & ~tt[0];
-                uint32_t res = (e67 & (~tt[0] | Cc)) | (Cc & e8);
-                if (!interior) {
-                    const int32_t gy = ys + y, gz = zs + z;
-                    res &= (gy < 0 || gz < 0) ? 0u : ca2k_keep_bits(gx, gy + gz, n);
-                }
-                pend = res;
-#pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    Sp[b] = Sc[b];
-                    Sc[b] = Sn[b];
-                }
-                Cc = Cn;
-            }
-            if (i & 1) __syncthreads();
-        }
-        if (steps & 1) __syncthreads();            // (uniform) every step's reads are done
-        if (active && za <= zb) {
-            buf[zb][y][c] = pend;                   // the part's last new plane
-            if (part > 0 && zb > za) buf[za][y][c] = first;
-        }
-        __syncthreads();
-    }
-
-    // 3. Write the tile: 16 cells per lane-step, rho / 16 per tile row.
-    constexpr int LPR = RHO / 16;
-    for (int q = tid; q < RHO * RHO * LPR; q += NT) {
-        const int lc = q % LPR, yy = (q / LPR) % RHO, zz = q / (LPR * RHO);
-        const int32_t gy = y0 + yy, gz = z0 + zz, x = x0 + 16 * lc;
-        const int32_t v = n - gy - gz - x + 1;
-        if (gy + gz > n || v <= 0) continue;
-        const int b = KH + 16 * lc;                   // region bit of the first cell
-        const uint32_t bits = buf[KH + zz][KH + yy][b / 32] >> (b % 32);
-        const uint32_t w0 = unpack4(bits), w1 = unpack4(bits >> 4), w2 = unpack4(bits >> 8),
-                       w3 = unpack4(bits >> 12);
-        uint8_t *row = out + (int64_t)gz * p2 + (int64_t)gy * p1;
-        if (v >= 16) {
-            *reinterpret_cast<uint4 *>(row + x) = make_uint4(w0, w1, w2, w3);
         } else {
-            const int32_t r = gy + gz;
-            st_masked(row, x, r, n, w0);
-            st_masked(row, x + 4, r, n, w1);
-            st_masked(row, x + 8, r, n, w2);
-            st_masked(row, x + 12, r, n, w3);
+            v = *reinterpret_cast<const uint4 *>(in + (has ? (int64_t)z * p2 + loff : (int64_t)0));
+        }
+        return v;
+    };
+    const int lat = (lr / R) * GP + (lr % R) * XW + lc / 2;   // LDS word of the piece
+    auto commit = [&](int32_t z, const uint4 &v, int slot) {
+        const uint32_t w = (pack16(v) << lup) & ca2k_row_bits(lleft, n - z - ly - lx, ly);
+        reinterpret_cast<uint16_t *>(&buf[slot][0][lat])[lc % 2] = (uint16_t)w;
+    };
+
+    // Storing: the thread's 16-cell piece of the tile.
+    const int32_t sx = x0 + 16 * lc, sy = y0 + lr;
+    const bool stores = lr < rho && 16 * lc < rho;
+    const int sb = (halo + 16 * lc) & 31, sw = (halo + 16 * lc) >> 5;
+    const int sat = ((halo + lr) / R) * GP + ((halo + lr) % R) * XW;
+    auto store = [&](int32_t z, int slot) {
+        const int32_t v = n - z - sy - sx + 1;         // simplex cells from sx on
+        if (!stores || v <= 0) return;
+        const uint32_t *pl = buf[slot][gens];
+        const uint32_t w = __builtin_amdgcn_alignbit(pl[sat + min(sw + 1, XW - 1)], pl[sat + sw], sb);
+        uint32_t w4[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) w4[i] = unpack4(w >> (4 * i));
+        uint8_t *row = out + (int64_t)z * p2 + (int64_t)sy * p1;
+        if (v >= 16) {
+            *reinterpret_cast<uint4 *>(row + sx) = make_uint4(w4[0], w4[1], w4[2], w4[3]);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) st_masked(row, sx + 4 * i, sy + z, n, w4[i]);
+        }
+    };
+
+    // Stepping: the lane's R words of its generation's planes.
+    const int gt = tid % (64 * WPG), xw = gt % XW, yg = gt / XW;
+    const int32_t gx = xs + 32 * xw, gy = ys + yg * R;
+    // cells with x >= 0; the halo being a multiple of R, a lane's rows are all
+    // below y = 0 or none is
+    const uint32_t left = gy >= 0 ? ca2k_left_bits(gx) : 0u;
+    const int32_t last = n - gx - gy;                 // row r, plane z: cells 0 .. last - r - z are inside
+    const int32_t za = max(0, z0 - (gens - gen)), zb = min(ztop, z1 + (gens - gen));   // the generation's planes
+    const int up = yg > 0 ? (yg - 1) * GP + (R - 1) * XW + xw : xw;          // (the region's edge rows go stale)
+    const int mid = yg * GP + xw;
+    const int dn = yg < YG - 1 ? (yg + 1) * GP + xw : mid + (R - 1) * XW;
+    auto hsum = [&](uint32_t c, uint32_t &s0, uint32_t &s1) {
+        constexpr int kPrev = XW == 4 ? 0x90 : 0xA0, kNext = XW == 4 ? 0xF9 : 0xF5;   // quad_perm: x-1, x+1
+        const uint32_t l = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)c, kPrev, 0xf, 0xf, true);
+        const uint32_t r = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)c, kNext, 0xf, 0xf, true);
+        const uint32_t L = __builtin_amdgcn_alignbit(c, l, 31);    // cell x-1
+        const uint32_t Rt = __builtin_amdgcn_alignbit(r, c, 1);    // cell x+1
+        s0 = xor3(L, c, Rt);
+        s1 = maj3(L, c, Rt);
+    };
+    // Reads plane z + 1 of the generation below from slot `rd`, makes plane z
+    // in slot `wr` (the two before the generation's first are made from less
+    // and never read); Sp and Sc hold the sums of planes z - 1 and z, C plane
+    // z; Sp is left with the sums of plane z + 1.
+    auto advance = [&](int32_t z, Ca3kSum (&Sp)[R], Ca3kSum (&Sc)[R], uint32_t (&C)[R], int rd, int wr) {
+        uint32_t w[R + 2];
+        const uint32_t *pl = buf[rd][gen - 1];
+        w[0] = pl[up];
+#pragma unroll
+        for (int r = 0; r < R; ++r) w[r + 1] = pl[mid + r * XW];
+        w[R + 1] = pl[dn];
+        uint32_t a0, a1, b0, b1;
+        hsum(w[0], a0, a1);
+        hsum(w[1], b0, b1);
+        // cells of row r inside the simplex: the low last - z - r + 1 bits, cut
+        // from those of row 0 as a 64-bit number
+        const int32_t lz0 = last - z;
+        const uint32_t klo = ca2k_row_bits(~0u, lz0, 0), khi = ca2k_row_bits(~0u, lz0 - 32, 0);
+        uint32_t *po = buf[wr][gen];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            uint32_t c0, c1;
+            hsum(w[r + 2], c0, c1);
+            Ca3kSum S;
+            S.q = xor3(a0, b0, c0);
+            S.k = maj3(a0, b0, c0);
+            S.t = xor3(a1, b1, c1);
+            S.m = maj3(a1, b1, c1);
+            po[mid + r * XW] = ca3k_rule(Sp[r], Sc[r], S, C[r], left, __builtin_amdgcn_alignbit(khi, klo, r));
+            Sp[r] = S;
+            C[r] = w[r + 1];
+            a0 = b0; a1 = b1;
+            b0 = c0; b1 = c1;
+        }
+    };
+
+    Ca3kSum SA[R] = {}, SB[R] = {};
+    uint32_t C[R] = {};
+    const int32_t s0 = max(0, z0 - gens) & ~1;         // first step (even: the parity of a step is its slot's)
+    const int32_t s1 = z1 + 2 * gens + 1;              // last: stores plane z1
+    const int32_t zl = min(ztop, z1 + gens);          // last plane loaded
+    constexpr int PF = R >= 8 ? 1 : 2;                 // steps that loads run ahead (the registers allow one at R = 8)
+    uint4 next[PF];
+#pragma unroll
+    for (int h = 0; h < PF; ++h) next[h] = load(s0 + h);
+    const bool steps = gen <= gens;
+    for (int32_t s = s0; s <= s1; s += 2) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int32_t sc = s + h, z = sc - 2 * gen;
+            if (steps && z + 1 >= max(0, za - 1) && z <= zb) {   // uniform
+                if (h == 0) advance(z, SA, SB, C, 1, 0);
+                else advance(z, SB, SA, C, 0, 1);
+            }
+            if (sc <= zl) {
+                if (loads) commit(sc, next[h % PF], h);
+                next[h % PF] = load(sc + PF);
+            }
+            const int32_t zo = sc - 1 - 2 * gens;
+            if (zo >= z0 && zo <= z1) store(zo, 1 - h);
+            lds_barrier();
         }
     }
 }
 
-// (the launch bound is Ca3kShape<RHO, KH>::NT, written without commas)
-template <int RHO, int KH, bool BB, bool SAFE>
-__global__ __launch_bounds__(3 * ((((RHO + 2 * KH) / 32 * (RHO + 2 * KH - 2) + 63) / 64) * 64)) void k_ca3k(
-    const Plan P, const uint8_t *__restrict__ in, uint8_t *__restrict__ out, int gens)
+template <int XW, int R, int WPG, bool SAFE>
+__global__ __launch_bounds__(1024, R >= 4 ? 4 : 8) void k_ca3k(const Plan P, const uint8_t *__restrict__ in,
+                                               uint8_t *__restrict__ out, int gens, int rz, const Ca3kUnits U)
 {
-    static_assert(3 * ((((RHO + 2 * KH) / 32 * (RHO + 2 * KH - 2) + 63) / 64) * 64) == Ca3kShape<RHO, KH>::NT,
-                  "launch bound");
+    const uint32_t u = U.unit[blockIdx.x];
+    ca3k_tile<XW, R, WPG, SAFE>(P, in, out, u & 1023u, u >> 10 & 1023u, u >> 20, gens, rz);
+}
+
+// The bounding box of columns and pieces.
+template <int XW, int R, int WPG, bool SAFE>
+__global__ __launch_bounds__(1024, R >= 4 ? 4 : 8) void k_ca3k_bb(const Plan P, const uint8_t *__restrict__ in,
+                                                  uint8_t *__restrict__ out, int gens, int rz)
+{
     int32_t t[4] = {0, 0, 0, 0};
     const WgId g = wg_id(P);
-    if (BB) {
-        decode_bb(P, g.x, g.y, g.z, t);
-    } else {
-        if (!decode_h<3>(P, g.x, t)) return;
-    }
-    ca3k_tile<RHO, KH, SAFE>(P, in, out, t, gens);
+    decode_bb(P, g.x, g.y, 0, t);
+    ca3k_tile<XW, R, WPG, SAFE>(P, in, out, t[0], t[1], (int32_t)g.z, gens, rz);
 }
 
 }  // namespace smap

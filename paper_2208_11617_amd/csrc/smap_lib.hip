@@ -157,8 +157,8 @@ struct CachedPlan {
 };
 std::map<std::tuple<int, int64_t, int, int, int, int, int>, CachedPlan> g_plans;  // (m,n,beta,rho,bb,cls,layout)
 // H native layout for m = 3 (simplex_set_layout); SMAP_LAYOUT_AUTO: the
-// level-ordered layout for one-job CA3 launches (one step or several
-// generations) and their plans, the packed one for everything else
+// level-ordered layout for one-job CA3 launches of one step and their plans,
+// the packed one for everything else
 int g_layout3 = SMAP_LAYOUT_AUTO;
 int g_general = 0;  // H launch of the pieces: 0 fused, 1 one launch per piece (simplex_set_general)
 
@@ -1341,9 +1341,97 @@ int steps2_region(int64_t n, int gens)
     return k * (k + 1) / 2 * (gens + 8) <= 48000 ? 128 : 256;
 }
 
-// CA3: 64^3 tiles, 16-cell halo (16 generations per pass), one bit per cell
-constexpr int kSteps3Rho = 64, kSteps3Kh = 16;
-constexpr TileCfg kSteps3Tile = {kSteps3Rho, Ca3kShape<kSteps3Rho, kSteps3Kh>::NT, 1};
+// CA3: a workgroup's region is W x W cells (Ca3kShape) and streams rz planes.
+template <int XW, int R, int WPG, bool SAFE>
+void launch_ca3k(const Ca3kUnits *units, const Plan &P, dim3 grid, const uint8_t *in, uint8_t *out, int gens, int rz,
+                 hipStream_t s)
+{
+    const dim3 nt((uint32_t)Ca3kShape<XW, R, WPG>::threads(gens));
+    if (units)
+        hipLaunchKernelGGL((k_ca3k<XW, R, WPG, SAFE>), grid, nt, 0, s, P, in, out, gens, rz, *units);
+    else
+        hipLaunchKernelGGL((k_ca3k_bb<XW, R, WPG, SAFE>), grid, nt, 0, s, P, in, out, gens, rz);
+}
+
+// The launch of one pass: the widest form first (the lanes of a generation
+// are spread over more waves where the pass has few generations).
+void dispatch_ca3k(int w, const Ca3kUnits *units, const Plan &P, dim3 grid, const uint8_t *in, uint8_t *out, int gens,
+                   int rz, hipStream_t s)
+{
+    if (P.n < 15) launch_ca3k<2, 2, 1, true>(units, P, grid, in, out, gens, rz, s);
+    else if (w == 128 && gens > 8) launch_ca3k<4, 8, 1, false>(units, P, grid, in, out, gens, rz, s);
+    else if (w == 128 && gens > 4) launch_ca3k<4, 4, 2, false>(units, P, grid, in, out, gens, rz, s);
+    else if (w == 128) launch_ca3k<4, 2, 4, false>(units, P, grid, in, out, gens, rz, s);
+    else if (gens > 8) launch_ca3k<2, 2, 1, false>(units, P, grid, in, out, gens, rz, s);
+    else launch_ca3k<2, 1, 2, false>(units, P, grid, in, out, gens, rz, s);
+}
+
+// Pieces of at most rz planes in the columns of rho x rho cells of Delta_n^3:
+// s + 1 columns are n - rho s + 1 planes high.
+int64_t steps3_pieces(int64_t n, int rho, int64_t rz)
+{
+    int64_t c = 0;
+    for (int64_t s = 0; s * rho <= n; ++s) c += (s + 1) * ((n - rho * s + rz) / rz);
+    return c;
+}
+
+// Launch plan of a pass of `gens` generations over Delta_n^3.
+struct Steps3Plan {
+    int w, rho, rz;                // region side, column side, planes of a piece at most
+    std::vector<uint32_t> units;   // H: the pieces (Ca3kUnits), tallest first
+};
+
+// W: 128-cell regions keep more of what they step; below n = 384 they leave
+// too few columns, and the planes of a generation, one after another, are the
+// time.  Measured (us; 64, 128): n = 200, 8 generations 19, 27 and 16: 42, 68;
+// n = 301: 27, 32 and 62, 76; n = 400: 40, 41 and 97, 89; n = 512: 56, 54.
+// rz: a workgroup fills a CU (two do with 64-cell regions and few
+// generations), and a pass over the chip takes the time of a piece, rz planes
+// and about 2 gens more to fill and drain the pipeline of generations; so the
+// pieces are made as tall as 1 to 8 whole rounds over the chip's 256 CUs allow,
+// whichever is shortest.  n = 1024, 16 generations: 340 us with 256
+// pieces, 372 with 512, 501 with 1024; 547 with pieces of 48 planes.
+Steps3Plan steps3_plan(int64_t n, int gens)
+{
+    Steps3Plan S;
+    S.w = n < 384 ? 64 : 128;
+    S.rho = ca3k_rho(S.w, gens);
+    const int64_t slots = S.w == 64 && gens <= 4 ? 512 : 256;
+    int64_t best = 0;
+    for (int64_t r = 1; r <= 8; ++r) {
+        int64_t lo = 1, hi = n + 1;                  // the lowest pieces of which there are at most r * slots
+        while (lo < hi) {
+            const int64_t mid = (lo + hi) / 2;
+            if (steps3_pieces(n, S.rho, mid) <= r * slots) hi = mid;
+            else lo = mid + 1;
+        }
+        const int64_t cost = r * (lo + 2 * gens);
+        if (r == 1 || cost < best) {
+            best = cost;
+            S.rz = (int)lo;
+        }
+    }
+    return S;
+}
+
+// The pieces of an H pass, tallest first, from the host run of the H map over
+// the columns (P: its plan).
+void steps3_units(const Plan &P, Steps3Plan &S)
+{
+    std::vector<std::pair<int32_t, uint32_t>> v;      // (-height, unit)
+    for (uint32_t w = 0; w < P.total; ++w) {
+        int32_t t[4] = {0, 0, 0, 0};
+        if (!decode_h<2>(P, w, t)) continue;
+        const int32_t height = P.n - P.rho * (t[0] + t[1]) + 1;
+        const int32_t pieces = (height + S.rz - 1) / S.rz, each = (height + pieces - 1) / pieces;
+        for (int32_t k = 0; k * each < height; ++k)
+            v.push_back({-std::min(each, height - k * each), (uint32_t)t[0] | (uint32_t)t[1] << 10 | (uint32_t)k << 20});
+    }
+    std::stable_sort(v.begin(), v.end(), [](const auto &a, const auto &b) { return a.first < b.first; });
+    S.units.reserve(v.size());
+    for (const auto &x : v) S.units.push_back(x.second);
+}
+std::map<std::pair<int64_t, int>, Steps3Plan> g_steps3;   // (n, generations of the longest pass); g_mu held
 
 int steps_launch(int m, int64_t n, int r, int beta, int op, int32_t steps, void *a, void *b,
                  void *stream, bool bb)
@@ -1362,21 +1450,35 @@ int steps_launch(int m, int64_t n, int r, int beta, int op, int32_t steps, void 
     if (rc != kOk) return rc;
     // passes of at most kh generations, alternating a -> b -> a ...;
     // an odd number of passes, so that the last one writes b
-    const int kh = ca3 ? kSteps3Kh : kCa2kMaxGens;
-    int passes = (steps + kh - 1) / kh;
+    const int kh = ca3 ? kCa3kMaxGens : kCa2kMaxGens;
+    int passes = (int)(((int64_t)steps + kh - 1) / kh);
     if (passes % 2 == 0) ++passes;
-    const int gmax = (steps + passes - 1) / passes;   // generations of the longest pass
-    const int w2 = ca3 ? 0 : steps2_region(n, gmax);
+    const int gmax = (int)(((int64_t)steps + passes - 1) / passes);   // generations of the longest pass
+    // one plane and two rows within the 3-D kernels' 32-bit offsets
+    if (ca3 && (__int128)(n + 1) * (n + 3) + 64 >= ((__int128)1 << 32)) return kErange;
+    // both run over 2-D tiles: the tiles of the 2-simplex, the columns of the 3-simplex
     Plan P;
+    Steps3Plan S3;
+    const int w2 = steps2_region(n, gmax);
     {
         std::lock_guard<std::mutex> lk(g_mu);
-        rc = plan_for(m, n, bt, bb, ca3 ? 2 : 1, ca3 ? kSteps3Tile : TileCfg{ca2k_rho(w2, gmax), 0, 1}, &P, nullptr,
-                      true);
+        if (ca3) {
+            auto it = g_steps3.find({n, gmax});
+            if (it == g_steps3.end()) {
+                if (g_steps3.size() >= 256) g_steps3.clear();
+                it = g_steps3.emplace(std::make_pair(n, gmax), steps3_plan(n, gmax)).first;
+            }
+            rc = plan_for(2, n, bt, bb, 1, TileCfg{it->second.rho, 0, 1}, &P, nullptr, true);
+            if (rc == kOk && !bb && it->second.units.empty()) steps3_units(P, it->second);
+            S3 = it->second;
+        } else {
+            rc = plan_for(2, n, bt, bb, 1, TileCfg{ca2k_rho(w2, gmax), 0, 1}, &P, nullptr, true);
+        }
     }
     if (rc != kOk) return rc;
     if (P.total == 0) return kOk;
     const uint32_t kb = (uint32_t)P.kbox;
-    const dim3 grid = bb ? dim3(kb, kb, ca3 ? kb : 1) : dim3(P.total, 1, 1);
+    const dim3 grid = bb ? dim3(kb, kb, ca3 ? (uint32_t)((n + S3.rz) / S3.rz) : 1) : dim3(P.total, 1, 1);
     P.grid[0] = grid.x;
     P.grid[1] = grid.y;
     P.grid[2] = grid.z;
@@ -1391,14 +1493,14 @@ int steps_launch(int m, int64_t n, int r, int beta, int op, int32_t steps, void 
         const uint8_t *src = (const uint8_t *)((i & 1) ? b : a);
         uint8_t *dst = (uint8_t *)((i & 1) ? a : b);
         const bool safe = n < 15;
-        constexpr int nt3 = Ca3kShape<kSteps3Rho, kSteps3Kh>::NT;
-        if (ca3) {
-            if (bb) {
-                if (safe) hipLaunchKernelGGL((k_ca3k<kSteps3Rho, kSteps3Kh, true, true>), grid, dim3(nt3), 0, s, P, src, dst, g);
-                else hipLaunchKernelGGL((k_ca3k<kSteps3Rho, kSteps3Kh, true, false>), grid, dim3(nt3), 0, s, P, src, dst, g);
-            } else {
-                if (safe) hipLaunchKernelGGL((k_ca3k<kSteps3Rho, kSteps3Kh, false, true>), grid, dim3(nt3), 0, s, P, src, dst, g);
-                else hipLaunchKernelGGL((k_ca3k<kSteps3Rho, kSteps3Kh, false, false>), grid, dim3(nt3), 0, s, P, src, dst, g);
+        if (ca3 && bb) {
+            dispatch_ca3k(S3.w, nullptr, P, grid, src, dst, g, S3.rz, s);
+        } else if (ca3) {
+            for (size_t o = 0; o < S3.units.size(); o += kCa3kUnits) {
+                Ca3kUnits U;
+                const size_t cnt = std::min<size_t>(kCa3kUnits, S3.units.size() - o);
+                std::copy(S3.units.begin() + o, S3.units.begin() + o + cnt, U.unit);
+                dispatch_ca3k(S3.w, &U, P, dim3((uint32_t)cnt), src, dst, g, S3.rz, s);
             }
         } else if (safe) {   // (a small board: 128-cell regions)
             launch_ca2k<4, 2, 4, true>(bb, P, grid, src, dst, g, s);

@@ -160,3 +160,28 @@ def test_steps_3d_workload_size_matches_single_steps(smap):
     assert torch.equal(out[inside], ref_a[inside])
     assert bool((out[~inside] == si.SENTINEL_U8).all())
     assert torch.equal(a, orig)
+
+
+@pytest.mark.parametrize("kind", ["h", "bb"])
+@pytest.mark.parametrize("n,steps", [
+    # 64-cell regions: columns of 48 (up to 8 generations) and 32 cells, two
+    # waves or one per generation; sizes at and beside a column's edge
+    (143, 8), (144, 7), (145, 1), (159, 16), (160, 9), (161, 12), (383, 5),
+    # 128-cell regions: columns of 112 (4 and 2 waves per generation) and 96
+    (384, 4), (447, 3), (448, 8), (449, 5), (479, 16), (480, 15), (481, 9), (700, 13)])
+def test_steps_3d_regions(smap, kind, n, steps):
+    """Both region widths of the 3-D pass and every split of its waves against
+    single-step launches."""
+    a = si.box_torch(3, n, "bern", 8300 + n, p=0.25, device="cuda")
+    x, y = a.clone(), a.clone()
+    for _ in range(steps):
+        smap.map_launch(3, n, "ca3", x, y)
+        x, y = y, x
+    out = si.sentinel_box_torch(3, n, True, device="cuda")
+    say(f"3-D {kind} n={n} steps={steps}")
+    (smap.map_launch_steps if kind == "h" else smap.bb_launch_steps)(3, n, "ca3", steps, a, out)
+    torch.cuda.synchronize()
+    r = torch.arange(n + 1, device="cuda", dtype=torch.int16)
+    inside = (r.view(-1, 1, 1) + r.view(1, -1, 1) + r.view(1, 1, -1)) <= n
+    assert torch.equal(out[inside], x[inside])
+    assert bool((out[~inside] == si.SENTINEL_U8).all())
