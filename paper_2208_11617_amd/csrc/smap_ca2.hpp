@@ -69,20 +69,30 @@ __device__ __forceinline__ uint32_t ld_masked(const uint8_t *row, int32_t x, int
     return v >= 4 ? d : (d & ((1u << (8 * v)) - 1u));
 }
 
-__device__ __forceinline__ void st_masked(uint8_t *row, int32_t x, int32_t r, int32_t n,
-                                          uint32_t val)
+// Stores the first v (1 .. 15) of the 16 cells r at p: the lane the
+// hypotenuse cuts.  One piece per binary digit of v, at most four stores and
+// no loop.  (Four bytes at a time with a byte-wise rest took up to a dozen
+// branches; with rows of a few hundred cells half of all waves hold such a
+// lane.)
+__device__ __forceinline__ void st_tail(uint8_t *p, uint32_t r0, uint32_t r1, uint32_t r2, uint32_t r3, int32_t v)
 {
-    const int32_t v = n - r - x + 1;
-    if (r < 0 || v <= 0) return;
-    if (v >= 4) {
-        st_u32(row + x, val);
-    } else {
-        // at most 3 bytes; unrolled (no loop), so every path issues a bounded
-        // number of stores and the wait counts before later loads stay exact
-#pragma unroll
-        for (int k = 0; k < 3; ++k)
-            if (k < v) row[x + k] = (uint8_t)(val >> (8 * k));
+    if (v & 8) {
+        *reinterpret_cast<uint2 *>(p) = make_uint2(r0, r1);
+        r0 = r2;
+        r1 = r3;
+        p += 8;
     }
+    if (v & 4) {
+        st_u32(p, r0);
+        r0 = r1;
+        p += 4;
+    }
+    if (v & 2) {
+        *reinterpret_cast<uint16_t *>(p) = (uint16_t)r0;
+        r0 >>= 16;
+        p += 2;
+    }
+    if (v & 1) *p = (uint8_t)r0;
 }
 
 // Life B3/S23 on four byte cells: t = 3x3 sum including the centre (<= 9),
@@ -241,9 +251,7 @@ __device__ __forceinline__ void ca2_tile(const Plan &P, const uint8_t *__restric
             uint8_t *rowp = out + (int64_t)(ywave + r) * pitch;    // wave-uniform
             *reinterpret_cast<uint4 *>(rowp + off_c) = make_uint4(res[0], res[1], res[2], res[3]);
         } else {
-            uint8_t *row = out + (int64_t)y * pitch;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) st_masked(row, x + 4 * i, y, n, res[i]);
+            st_tail(out + (int64_t)y * pitch + x, res[0], res[1], res[2], res[3], v);
         }
     };
     auto load_row = [&](int32_t r, uint32_t *c, uint32_t &e) {

@@ -241,8 +241,7 @@ __device__ __forceinline__ void ca3_tile(const Plan &P, const uint8_t *__restric
                     if (v >= 16) {
                         *reinterpret_cast<uint4 *>(row + x) = make_uint4(res[0], res[1], res[2], res[3]);
                     } else {
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) st_masked(row, x + 4 * k, yj + z, n, res[k]);
+                        st_tail(row + x, res[0], res[1], res[2], res[3], v);
                     }
                 }
             }

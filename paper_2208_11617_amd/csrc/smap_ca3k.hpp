@@ -177,8 +177,7 @@ __device__ __forceinline__ void ca3k_tile(const Plan &P, const uint8_t *__restri
         if (v >= 16) {
             *reinterpret_cast<uint4 *>(row + sx) = make_uint4(w4[0], w4[1], w4[2], w4[3]);
         } else {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) st_masked(row, sx + 4 * i, sy + z, n, w4[i]);
+            st_tail(row + sx, w4[0], w4[1], w4[2], w4[3], v);
         }
     };
 
