@@ -24,6 +24,7 @@
 #include "smap_copy.hpp"
 #include "smap_plan.hpp"
 #include "smap_point.hpp"
+#include "smap_rows.hpp"
 #include "smap_serve.hpp"
 
 using namespace smap;
@@ -87,7 +88,7 @@ constexpr Ca3Shape kCa3Shapes[] = {
     {32, 64, 32, ca3_rz(32), 1, (32 / 32) * (32 / ca3_rz(32))},
 };
 
-// op class: 0 = pointwise (MAP/ACCUM/HITS/HASH), 1 = CA2, 2 = CA3
+// op class: 0 = pointwise (MAP/ACCUM/HITS/HASH/EDM), 1 = CA2, 2 = CA3
 int op_class(int op) { return op == OP_CA2 ? 1 : (op == OP_CA3 ? 2 : 0); }
 
 // CA3: 256^3 tiles from n = 768 on; below, 128^3 (with only two or three
@@ -162,10 +163,17 @@ std::map<std::tuple<int, int64_t, int, int, int, int, int>, CachedPlan> g_plans;
 int g_layout3 = SMAP_LAYOUT_AUTO;
 int g_general = 0;  // H launch of the pieces: 0 fused, 1 one launch per piece (simplex_set_general)
 
-TileCfg tile_for(int m, int64_t n, int cls)
+// EDM: 64-cell tiles from n = 6000 on (four rows share a lane's points, and a
+// tile row is two lines): n = 8000 45 -> 35 us, 12000 84 -> 70, 16384
+// 162 -> 117; at n = 4000 15.4 and 15.5.
+constexpr int64_t kEdmLargeTileN = 6000;
+
+TileCfg tile_for(int m, int64_t n, int op)
 {
-    auto it = g_tiles.find({m, cls});
-    return it != g_tiles.end() ? it->second : default_tile(m, n, cls);
+    auto it = g_tiles.find({m, op_class(op)});
+    if (it != g_tiles.end()) return it->second;
+    if (op == OP_EDM && n >= kEdmLargeTileN) return {64, 256, 1};
+    return default_tile(m, n, op_class(op));
 }
 
 // Autotuned H choices per (m, n, op class) (g_mu held when used).
@@ -175,10 +183,10 @@ struct Tuned {
 };
 std::map<std::tuple<int, int64_t, int>, Tuned> g_tuned;
 
-TileCfg tile_for_h(int m, int64_t n, int cls)
+TileCfg tile_for_h(int m, int64_t n, int op)
 {
-    auto it = g_tuned.find(std::make_tuple(m, n, cls));
-    return it != g_tuned.end() ? it->second.t : tile_for(m, n, cls);
+    auto it = g_tuned.find(std::make_tuple(m, n, op_class(op)));
+    return it != g_tuned.end() ? it->second.t : tile_for(m, n, op);
 }
 
 int resolve_rb(int m, int r, int beta, int *beta_out)
@@ -255,7 +263,7 @@ int get_plan(int m, int64_t n, int beta, int op, bool bb, Plan *P, PlanCounts *C
 {
     const int cls = op_class(op);
     std::lock_guard<std::mutex> lk(g_mu);
-    const TileCfg t = bb ? tile_for(m, n, cls) : tile_for_h(m, n, cls);
+    const TileCfg t = bb ? tile_for(m, n, op) : tile_for_h(m, n, op);
     *tc = t;
     return plan_for(m, n, beta, bb, cls, t, P, C, true);
 }
@@ -341,6 +349,25 @@ void launch_point_grp(const Plan &P, dim3 grid, const void *in, void *out, hipSt
                        (const uint32_t *)in, (uint32_t *)out);
 }
 
+template <int OP, int RHO, int NT, int SUB, bool BB>
+void launch_rows(const Plan &P, dim3 grid, const void *in, void *out, hipStream_t s)
+{
+    hipLaunchKernelGGL((k_rows<OP, RHO, NT, SUB, BB>), grid, dim3(NT), 0, s, P, (const uint32_t *)in, (uint32_t *)out);
+}
+
+// ACCUM, HASH and EDM on 2-D tiles, one tile or part of a tile per workgroup.
+template <int OP, bool BB>
+int dispatch_rows(const TileCfg &tc, const Plan &P, dim3 grid, const void *in, void *out, hipStream_t s)
+{
+    if (tc.rho == 32 && tc.wg == 256) launch_rows<OP, 32, 256, 1, BB>(P, grid, in, out, s);
+    else if (tc.rho == 16) launch_rows<OP, 16, 64, 1, BB>(P, grid, in, out, s);
+    else if (tc.rho == 64) launch_rows<OP, 64, 256, 1, BB>(P, grid, in, out, s);
+    else if (tc.rho == 128) launch_rows<OP, 128, 256, 2, BB>(P, grid, in, out, s);
+    else if (OP == OP_EDM && tc.rho == 32) launch_rows<OP, 32, 256, 1, BB>(P, grid, in, out, s);
+    else return kEunsupported;
+    return kOk;
+}
+
 template <int OP, bool BB>
 int dispatch_point_shape(int m, const TileCfg &tc, const Plan &P, dim3 grid, const void *in, void *out,
                          hipStream_t s)
@@ -387,21 +414,21 @@ template <bool BB>
 int dispatch_point(int op, int m, const TileCfg &tc, const Plan &P, dim3 grid, const void *in, void *out,
                    hipStream_t s)
 {
+    // (the one-wave and grouped 2-D shapes stay with the general kernels)
+    const bool rows = m == 2 && tc.grp == 1 && !(tc.rho == 32 && tc.wg != 256);
     switch (op) {
     case OP_MAP: return dispatch_point_shape<OP_MAP, BB>(m, tc, P, grid, in, out, s);
-    case OP_ACCUM: return dispatch_point_shape<OP_ACCUM, BB>(m, tc, P, grid, in, out, s);
+    case OP_ACCUM:
+        if (rows) return dispatch_rows<OP_ACCUM, BB>(tc, P, grid, in, out, s);
+        return dispatch_point_shape<OP_ACCUM, BB>(m, tc, P, grid, in, out, s);
     case OP_HITS: return dispatch_point_shape<OP_HITS, BB>(m, tc, P, grid, in, out, s);
-    case OP_HASH: return dispatch_point_shape<OP_HASH, BB>(m, tc, P, grid, in, out, s);
+    case OP_HASH:
+        if (rows) return dispatch_rows<OP_HASH, BB>(tc, P, grid, in, out, s);
+        return dispatch_point_shape<OP_HASH, BB>(m, tc, P, grid, in, out, s);
     case OP_EDM:
         if (m != 2) return kEinval;
         if (tc.grp != 1) return kEunsupported;       // one tile per workgroup only
-        switch (tc.rho) {
-        case 32: launch_point<2, 32, 256, 1, OP_EDM, BB>(P, grid, in, out, s); return kOk;
-        case 16: launch_point<2, 16, 64, 1, OP_EDM, BB>(P, grid, in, out, s); return kOk;
-        case 64: launch_point<2, 64, 256, 1, OP_EDM, BB>(P, grid, in, out, s); return kOk;
-        case 128: launch_point<2, 128, 256, 2, OP_EDM, BB>(P, grid, in, out, s); return kOk;
-        }
-        return kEunsupported;
+        return dispatch_rows<OP_EDM, BB>(tc, P, grid, in, out, s);
     }
     return kEinval;
 }

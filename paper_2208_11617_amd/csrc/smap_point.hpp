@@ -1,10 +1,7 @@
-// smap_point.hpp -- per-element kernels MAP, ACCUM, HITS, HASH (uint32) and
-// EDM (float32).
+// smap_point.hpp -- per-element kernels MAP, ACCUM, HITS, HASH (uint32).
 //
-// The test kernels of Section 5.1, Table tab:tests, plus HITS and HASH.  EDM
-// (2-D only) stores at element (x_1, x_2) the distance between points
-// i = x_1 and j = n - x_2 of a set of n+1 points in R^3 (x_1 + x_2 <= n is
-// i <= j), in float32: three differences, a sum of squares, sqrtf.
+// The test kernels of Section 5.1, Table tab:tests, plus HITS and HASH (on most
+// 2-D tiles ACCUM and HASH run in smap_rows.hpp instead, with EDM).
 // The tile comes from the H decode (one 1-D grid over the fused native +
 // shell pieces) or from the BB grid coordinates; BB tiles fully outside the
 // simplex exit before touching memory.
@@ -62,7 +59,7 @@ __device__ __forceinline__ uint32_t hash32_words(const int32_t *x)
 // hpre[j] is the FNV-1a state after words x_1 + j, x_2 .. x_KF, common to
 // the lane's rows.
 template <int M, int OP, int KF = 0>
-__device__ __forceinline__ void point_lane(int32_t n, const uint32_t *in, const uint32_t *pin, uint32_t *pout,
+__device__ __forceinline__ void point_lane(const uint32_t *pin, uint32_t *pout,
                                            uint32_t off, int32_t v, int32_t (&xr)[M],
                                            const uint32_t (&hpre)[4] = {0u, 0u, 0u, 0u})
 {
@@ -84,35 +81,6 @@ __device__ __forceinline__ void point_lane(int32_t n, const uint32_t *in, const 
             }
 #pragma unroll
             for (int j = 0; j < 4; ++j) r[j] += 1u;
-        } else if (OP == OP_EDM) {
-            if constexpr (M == 2) {
-                // element (x_1, x_2) holds d(p_i, p_j), i = x_1, j = n - x_2
-                const float *pts = reinterpret_cast<const float *>(in);
-                const int32_t jj = n - xr[1];
-                const float qx = pts[3 * jj], qy = pts[3 * jj + 1], qz = pts[3 * jj + 2];
-                auto dist = [&](float a, float b, float c) {
-                    const float dx = a - qx, dy = b - qy, dz = c - qz;
-                    return __float_as_uint(sqrtf(dx * dx + dy * dy + dz * dz));
-                };
-                const int32_t i0 = xr[0];
-                if (v >= 4) {  // points i0 .. i0+3: 12 floats, 16-byte aligned (i0 % 4 == 0)
-                    const float4 *q4 = reinterpret_cast<const float4 *>(pts + 3 * i0);
-                    const float4 a = q4[0], b = q4[1], c = q4[2];
-                    r[0] = dist(a.x, a.y, a.z);
-                    r[1] = dist(a.w, b.x, b.y);
-                    r[2] = dist(b.z, b.w, c.x);
-                    r[3] = dist(c.y, c.z, c.w);
-                } else {       // only the points inside: no read past point n
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const float *p = pts + 3 * (i0 + (j < v ? j : 0));
-                        r[j] = dist(p[0], p[1], p[2]);
-                    }
-                }
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) r[j] = 0u;
-            }
         } else if constexpr (KF > 0) {  // OP_HASH from the lane's common leading words
 #pragma unroll
             for (int j = 0; j < 4; ++j) r[j] = hash32_fmix(hash32_state<KF, M>(hpre[j], xr));
@@ -197,7 +165,7 @@ __global__ __launch_bounds__(NT) void k_point(const Plan P, const uint32_t *in, 
         }
         const int32_t v = n - rs + 1;                // elements of the lane inside the simplex
         if (v <= 0) continue;
-        point_lane<M, OP>(n, in, pin, pout, off, v, xr);
+        point_lane<M, OP>(pin, pout, off, v, xr);
     }
 }
 
@@ -306,7 +274,7 @@ __global__ __launch_bounds__(NT) void k_point_grp(const Plan P, const uint32_t *
         }
         const int32_t v = n - rs + 1;
         if (v <= 0) continue;
-        point_lane<M, OP, OP == OP_HASH ? KF : 0>(n, in, pin, pout, off, v, xr, hpre);
+        point_lane<M, OP, OP == OP_HASH ? KF : 0>(pin, pout, off, v, xr, hpre);
     }
 }
 

@@ -317,3 +317,12 @@ def test_set_shape_validation_and_grouped_counts():
         smap.set_tile(4, "hash", 0)
         smap.set_tile(3, "ca3", 0)
     assert smap.plan_info(4, 128, "hash")["tiles_per_wg"] == 2   # the default m = 4 shape
+
+
+def test_edm_default_tile():
+    """EDM takes 64-cell tiles from n = 6000 on; the other 2-D ops keep 32."""
+    from paper_2208_11617_amd import binding as smap
+    for use_bb in (False, True):
+        assert smap.plan_info(2, 5999, "edm", use_bb=use_bb)["rho"] == 32
+        assert smap.plan_info(2, 6000, "edm", use_bb=use_bb)["rho"] == 64
+        assert smap.plan_info(2, 6000, "accum", use_bb=use_bb)["rho"] == 32

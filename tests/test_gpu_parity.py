@@ -450,6 +450,34 @@ def test_edm_parity(smap):
         smap.set_tile(2, "edm", 0)
 
 
+@pytest.mark.parametrize("rho", [16, 32, 64, 128])
+@pytest.mark.parametrize("n", [127, 130, 161])
+def test_row_parts_any_alignment(smap, n, rho):
+    """ACCUM, HASH and EDM on 2-D tiles write line-aligned parts of rows: every
+    offset of the box from a line, against the same launch at offset 0 (compared
+    with the oracle elsewhere); the words around the box stay."""
+    words = (n + 1) ** 2
+    x = torch.from_numpy(si.box(2, n, "u31", 77 + n, poison=False).view(np.int32)).cuda().view(-1)
+    pts = torch.from_numpy(si.points(n, 78 + n)).cuda()
+    try:
+        for op in ("accum", "hash", "edm"):
+            smap.set_tile(2, op, rho)
+            src = {"accum": x, "hash": None, "edm": pts}[op]
+            for launch in (smap.map_launch, smap.bb_launch):
+                ref = None
+                for off in [0] + list(range(1, 33, 1 if rho == 32 else 5)):
+                    buf = torch.full((words + 64,), 7, dtype=torch.int32, device="cuda")
+                    launch(2, n, op, src, buf[off:off + words])
+                    torch.cuda.synchronize()
+                    got = buf[off:off + words].clone()
+                    ref = got if ref is None else ref
+                    assert torch.equal(got, ref), (op, off)
+                    assert bool((buf[:off] == 7).all()) and bool((buf[off + words:] == 7).all()), (op, off)
+    finally:
+        for op in ("accum", "hash", "edm"):
+            smap.set_tile(2, op, 0)
+
+
 def test_levels_layout_3d(smap):
     """The level-ordered 3-D layout: exactly-once hits and bit-exact CA3."""
     smap.set_layout(3, smap.LAYOUT_LEVELS)
