@@ -471,9 +471,10 @@ int dispatch(int m, int op, const TileCfg &tc, const Plan &P0, const void *in, v
     // H runs XCD-contiguous (its workgroups are nearly all useful, so every
     // XCD gets an equal share of the work) when neighbouring tiles share
     // cache lines: the pointwise ops that touch memory.  Measured faster in
-    // the hardware order: MAP (no memory traffic to share) and the automata
-    // (their sub-block order already spreads the concurrent workgroups over
-    // the buffer; 2-D: 66.8 against 69.6 us at n = 16384).  BB never splits
+    // the hardware order: MAP (no memory traffic to share) and the 2-D
+    // automaton (its sub-block order already spreads the concurrent workgroups
+    // over the buffer; 66.8 against 69.6 us at n = 16384).  The 3-D automaton
+    // takes runs of 64 ids per XCD (xcd_block).  BB never splits
     // contiguously (the XCDs at the end of the range would get mostly empty
     // box tiles).  For the automata it scatters each group of 8 ids over
     // the XCDs: the plain order ties the useful tile columns to a few XCDs
@@ -481,7 +482,7 @@ int dispatch(int m, int op, const TileCfg &tc, const Plan &P0, const void *in, v
     // against 106-172 us).  The pointwise ops keep the plain order (4-D
     // hash: 29.9 against 34.7 us scattered).
     PL.remap = BB ? ((op == OP_CA2 || op == OP_CA3) ? 2u : 0u)
-                  : ((op == OP_CA2 || op == OP_CA3 || op == OP_MAP) ? 0u : 1u);
+                  : (op == OP_CA3 ? 3u : ((op == OP_CA2 || op == OP_MAP) ? 0u : 1u));
     if (op == OP_CA2) {
         const uint8_t *i8 = (const uint8_t *)in;
         uint8_t *o8 = (uint8_t *)out;
