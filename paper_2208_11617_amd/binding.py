@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(PKG, "libsimplexmap.so")
@@ -174,7 +175,7 @@ def _check(status: int, what: str) -> None:
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()      # (an int: ctypes converts it by the argtypes)
 
 
 # Element types the kernels read and write, per op (torch dtype names).
@@ -195,15 +196,24 @@ def _need_bytes(op, m, n, which):
 
 
 _torch_mod = None
+_fast_dtypes = None        # _OP_DTYPES with torch's dtypes for their names
 
 
 def _torch():
     """torch, imported on first use (the host-only calls do not need it)."""
-    global _torch_mod
+    global _torch_mod, _fast_dtypes
     if _torch_mod is None:
         import torch
+        _fast_dtypes = {op: tuple(None if d is None else tuple(getattr(torch, x) for x in d) for d in pair)
+                        for op, pair in _OP_DTYPES.items()}
         _torch_mod = torch
     return _torch_mod
+
+
+def _good(t, dtypes, nbytes, tensor):
+    """Whether t passes every check of _check_tensor."""
+    return (isinstance(t, tensor) and t.dtype in dtypes and t.is_contiguous() and t.nbytes >= nbytes
+            and t.is_cuda)
 
 
 def _dtype_name(t):
@@ -238,6 +248,13 @@ def _check_op_buffers(what, m, n, op, buf_in, buf_out):
     op = _op(op)
     if op not in _OP_DTYPES or not isinstance(m, int) or not isinstance(n, int) or m < 2 or m > 4 or n < 0:
         return
+    # the launch's buffers are almost always right: one pass over them, and
+    # the checks one by one, which say what is wrong, only where it fails
+    tensor = _torch().Tensor
+    din, dout = _fast_dtypes[op]
+    if ((buf_in is None or din is None or _good(buf_in, din, _need_bytes(op, m, n, 0), tensor)) and
+            (buf_out is None or dout is None or _good(buf_out, dout, _need_bytes(op, m, n, 1), tensor))):
+        return
     din, dout = _OP_DTYPES[op]
     bufs = [(t, dt, which, role) for t, dt, which, role in
             ((buf_in, din, 0, "buf_in"), (buf_out, dout, 1, "buf_out")) if t is not None and dt is not None]
@@ -249,11 +266,16 @@ def _check_op_buffers(what, m, n, op, buf_in, buf_out):
 
 
 def _stream(stream):
+    """The hipStream_t of a stream (torch's or a raw handle), or of the current
+    stream of the current device."""
     if stream is None:
-        import torch
+        torch = _torch()
+        if torch.cuda.is_initialized():
+            # current_stream().cuda_stream without the Stream object (3 us)
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         stream = torch.cuda.current_stream()
     s = getattr(stream, "cuda_stream", stream)
-    return ctypes.c_void_p(int(s) if s else 0)
+    return int(s) if s else 0
 
 
 def map_launch(m, n, op, buf_in=None, buf_out=None, r=0, beta=0, stream=None) -> None:
@@ -315,16 +337,26 @@ def set_shape(m, op, rho, wg_threads=0, tiles_per_wg=0) -> None:
     _check(lib().simplex_set_shape(m, _op(op), rho, wg_threads, tiles_per_wg), "simplex_set_shape")
 
 
+_JOB = struct.Struct("@iiqPP")       # struct simplex_job
+assert _JOB.size == ctypes.sizeof(Job)
+
+
 def _job_array(jobs, what="simplex_batch_launch"):
     """jobs: iterable of (m, op, n, buf_in, buf_out) with tensors or raw
     pointers (raw pointers are passed as they are; tensors are validated)."""
     def p(x):
         return None if x is None else (x if isinstance(x, int) else x.data_ptr())
-    arr = (Job * max(len(jobs), 1))()
+    count = len(jobs)
+    raw = bytearray(_JOB.size * max(count, 1))
+    arr = (Job * max(count, 1)).from_buffer(raw)
     for i, (m, op, n, a, b) in enumerate(jobs):
         if not isinstance(a, int) and not isinstance(b, int):
             _check_op_buffers(what, m, n, op, a, b)
-        arr[i] = Job(m, _op(op), n, p(a), p(b))
+        pa, pb = p(a), p(b)
+        try:
+            _JOB.pack_into(raw, i * _JOB.size, m, _op(op), n, pa or 0, pb or 0)
+        except struct.error:           # a value that only ctypes converts (or refuses)
+            arr[i] = Job(m, _op(op), n, pa, pb)
     return arr
 
 

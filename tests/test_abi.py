@@ -326,3 +326,13 @@ def test_edm_default_tile():
         assert smap.plan_info(2, 5999, "edm", use_bb=use_bb)["rho"] == 32
         assert smap.plan_info(2, 6000, "edm", use_bb=use_bb)["rho"] == 64
         assert smap.plan_info(2, 6000, "accum", use_bb=use_bb)["rho"] == 32
+
+
+def test_job_array_fields():
+    """The packed job array holds the fields ctypes would (values outside a
+    field's range included: those wrap, as in struct simplex_job)."""
+    from paper_2208_11617_amd import binding as smap
+    arr = smap._job_array([(2, "ca2", 5, 1234, 5678), (3 + 2 ** 32, "ca3", -1, None, 7)])
+    assert [(j.m, j.op, j.n, j.buf_in, j.buf_out) for j in arr] == [
+        (2, smap.OP_CA2, 5, 1234, 5678), (3, smap.OP_CA3, -1, None, 7)]
+    assert len(smap._job_array([])) == 1
