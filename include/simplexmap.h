@@ -328,8 +328,8 @@ int simplex_copy_launch(int m, int64_t n, const void *buf_in, void *buf_out, voi
  * the chip and advances it as many generations as the halo is wide, so HBM is
  * read and written once per pass instead of once per generation.
  * Supported (others: SMAP_EUNSUPPORTED):
- *   m = 2, SMAP_OP_CA2: tiles of 64 to 240 cells a side inside regions of
- *     128 or 256 cells, chosen from n and the generations of a pass: up to
+ *   m = 2, SMAP_OP_CA2: tiles of 64 to 464 cells a side inside regions of
+ *     128, 256 or 512 cells, chosen from n and the generations of a pass: up to
  *     G = 32 per pass;
  *   m = 3, SMAP_OP_CA3: columns of 32 to 112 cells a side inside regions of
  *     64 or 128, found with the 2-D map, whose planes stream through the

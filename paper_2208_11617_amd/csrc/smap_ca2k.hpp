@@ -22,14 +22,10 @@
 // they are: about 14 operations (two 3-input logic operations per full
 // adder) step 32 cells.
 //
-// Bound: HBM up to about 8 generations a pass, the VALU from about 16 on.
-// A region kept in LDS and read back for every generation (256-cell tiles in
-// 320-cell regions) took 288 us for 32 generations at n = 16384 and 60 us for
-// 17 at n = 3001; this form takes 122 and 10 us.  256-cell regions of 8 waves
-// and 4 rows per lane: 512-cell ones (77 % instead of 56 % of what is stepped
-// is kept at 32 generations) ran 142-166 us in five splits, their 700 to 1400
-// workgroups filling the chip unevenly; 8 rows per lane and 4 waves (fewer
-// operations per row) 140 against 138 us at the time.
+// Bound: HBM up to about 16 generations a pass, the VALU above.  A region kept
+// in LDS and read back for every generation (256-cell tiles in 320-cell
+// regions) took 288 us for 32 generations at n = 16384 and 60 us for 17 at
+// n = 3001; this form takes 109 and 10 us.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -125,8 +121,8 @@ struct Ca2kShape {
     static constexpr int NG = (64 / XL) * NW;        // lane groups, one below the other
     static constexpr int NT = 64 * NW;
     static constexpr int RPI = NT / (2 * XL);        // rows the workgroup loads at once, 16 cells a lane
-    static constexpr int LB = W / RPI;               // pieces in flight per lane: the whole region
-    static_assert(64 % XL == 0 && NG * R == W && W % RPI == 0 && LB <= 8 && W > 2 * kCa2kMaxGens, "bad CA2K shape");
+    static constexpr int LB = W / RPI < 8 ? W / RPI : 8;   // pieces in flight per lane
+    static_assert(64 % XL == 0 && NG * R == W && W % (RPI * LB) == 0 && W > 2 * kCa2kMaxGens, "bad CA2K shape");
 };
 
 // Tile side that leaves a halo of at least `gens` cells in a region of W
@@ -163,31 +159,34 @@ __device__ __forceinline__ void ca2k_tile(const Plan &P, const uint8_t *__restri
         const int32_t rt = threadIdx.x / (2 * XL);
         const uint32_t left = ca2k_left_bits(xc);
         const uint32_t up16 = (uint32_t)min(max(-xc, 0), 31);
-        uint4 v[LB];
+#pragma unroll 1
+        for (int r0 = 0; r0 < W; r0 += RPI * LB) {
+            uint4 v[LB];
 #pragma unroll
-        for (int k = 0; k < LB; ++k) {
-            const int32_t yr = ys + k * RPI + rt;
-            const bool has = (yr >= 0) & (xc > -16) & (xa <= n - yr);
-            if constexpr (SAFE) {
-                v[k] = make_uint4(0u, 0u, 0u, 0u);
-                if (has) {
-                    const int64_t rb = (int64_t)yr * pitch;
-                    v[k].x = ld_masked(in + rb, xa, yr, n, total - rb);
-                    v[k].y = ld_masked(in + rb, xa + 4, yr, n, total - rb);
-                    v[k].z = ld_masked(in + rb, xa + 8, yr, n, total - rb);
-                    v[k].w = ld_masked(in + rb, xa + 12, yr, n, total - rb);
+            for (int k = 0; k < LB; ++k) {
+                const int32_t yr = ys + r0 + k * RPI + rt;
+                const bool has = (yr >= 0) & (xc > -16) & (xa <= n - yr);
+                if constexpr (SAFE) {
+                    v[k] = make_uint4(0u, 0u, 0u, 0u);
+                    if (has) {
+                        const int64_t rb = (int64_t)yr * pitch;
+                        v[k].x = ld_masked(in + rb, xa, yr, n, total - rb);
+                        v[k].y = ld_masked(in + rb, xa + 4, yr, n, total - rb);
+                        v[k].z = ld_masked(in + rb, xa + 8, yr, n, total - rb);
+                        v[k].w = ld_masked(in + rb, xa + 12, yr, n, total - rb);
+                    }
+                } else {
+                    const int64_t at = (int64_t)yr * pitch + xa;
+                    v[k] = *reinterpret_cast<const uint4 *>(in + (has ? at : 0));
                 }
-            } else {
-                const int64_t at = (int64_t)yr * pitch + xa;
-                v[k] = *reinterpret_cast<const uint4 *>(in + (has ? at : 0));
             }
-        }
 #pragma unroll
-        for (int k = 0; k < LB; ++k) {
-            const int r = k * RPI + rt;
-            const int32_t yr = ys + r;
-            const uint32_t w = (pack16(v[k]) << up16) & ca2k_row_bits(left, n - yr - xc, yr);
-            reinterpret_cast<uint16_t *>(&stage[r][0])[threadIdx.x % (2 * XL)] = (uint16_t)w;
+            for (int k = 0; k < LB; ++k) {
+                const int r = r0 + k * RPI + rt;
+                const int32_t yr = ys + r;
+                const uint32_t w = (pack16(v[k]) << up16) & ca2k_row_bits(left, n - yr - xc, yr);
+                reinterpret_cast<uint16_t *>(&stage[r][0])[threadIdx.x % (2 * XL)] = (uint16_t)w;
+            }
         }
     }
     lds_barrier();
@@ -263,7 +262,7 @@ __device__ __forceinline__ void ca2k_tile(const Plan &P, const uint8_t *__restri
 }
 
 template <int XL, int R, int NW, bool BB, bool SAFE>
-__global__ __launch_bounds__(64 * NW, 8) void k_ca2k(const Plan P, const uint8_t *__restrict__ in,
+__global__ __launch_bounds__(64 * NW, XL >= 16 ? 6 : 8) void k_ca2k(const Plan P, const uint8_t *__restrict__ in,
                                                      uint8_t *__restrict__ out, int gens)
 {
     int32_t t[4] = {0, 0, 0, 0};

@@ -1363,10 +1363,16 @@ void launch_ca2k(bool bb, const Plan &P, dim3 grid, const uint8_t *in, uint8_t *
 // 17 generations 9.6, 14.8; n = 3001, 17: 11.2, 15.0 (722 tiles of 80 cells);
 // n = 5000, 17: 21.1, 22.8 (1984); n = 3001, 32: 22.8, 21.6 (1104 of 64);
 // n = 8191, 8: 17.5, 19.4 (2738 of 112); n = 8191, 17: 42.5, 33.5 (5253).
+// 512 cells where the board fills the chip with such tiles (two of 448 cells
+// to a CU) and the generations, not memory, are the time: they keep 77 % of
+// what they step where 256 keep 56 %.  (256, 512): n = 16384, 32 generations
+// 124, 109; n = 20000, 32: 189, 168; but n = 16384, 17: 85, 91; n = 11000, 32:
+// 73, 79 (325 tiles).
 int steps2_region(int64_t n, int gens)
 {
-    const int64_t k = n / ca2k_rho(128, gens) + 1;
-    return k * (k + 1) / 2 * (gens + 8) <= 48000 ? 128 : 256;
+    const auto tiles = [&](int w) { const int64_t k = n / ca2k_rho(w, gens) + 1; return k * (k + 1) / 2; };
+    if (tiles(128) * (gens + 8) <= 48000) return 128;
+    return gens >= 24 && tiles(512) >= 600 ? 512 : 256;
 }
 
 // CA3: a workgroup's region is W x W cells (Ca3kShape) and streams rz planes.
@@ -1534,8 +1540,10 @@ int steps_launch(int m, int64_t n, int r, int beta, int op, int32_t steps, void 
             launch_ca2k<4, 2, 4, true>(bb, P, grid, src, dst, g, s);
         } else if (w2 == 128) {
             launch_ca2k<4, 2, 4, false>(bb, P, grid, src, dst, g, s);
-        } else {
+        } else if (w2 == 256) {
             launch_ca2k<8, 4, 8, false>(bb, P, grid, src, dst, g, s);
+        } else {
+            launch_ca2k<16, 16, 8, false>(bb, P, grid, src, dst, g, s);
         }
         if (hipGetLastError() != hipSuccess) return kEhip;
         left -= g;

@@ -93,9 +93,11 @@ def test_steps_workload_size_matches_single_steps(smap):
     # and one either side of a tile's edge; 208 (23); 240 (2)
     (3455, 32), (3456, 32), (3457, 31), (5200, 23), (10000, 2),
     # 128-cell regions at their largest boards: tiles of 64, 80 and 112 cells
-    (2999, 32), (4799, 24), (7503, 5)])
+    (2999, 32), (4799, 24), (7503, 5),
+    # 512-cell regions: tiles of 448 and 464 cells
+    (15231, 32), (15232, 31), (15800, 24)])
 def test_steps_region_widths(smap, kind, n, steps):
-    """Both region widths of the 2-D pass against single-step launches."""
+    """Every region width of the 2-D pass against single-step launches."""
     a = si.box_torch(2, n, "bern", 8200 + n, p=0.35, device="cuda")
     x, y = a.clone(), a.clone()
     for _ in range(steps):
