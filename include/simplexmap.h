@@ -400,7 +400,7 @@ int simplex_batch_launch(const struct simplex_job *jobs, int32_t njobs, void *st
  * Steps every job of `jobs[0..njobs)` with the H map in ONE persistent
  * launch for all classes (CA2 and CA3 jobs mixed), through a device-side
  * work queue of H-mapped block ranges.  A work unit is one H-mapped tile
- * (CA2, rho = 256) or one of the 4 sub-blocks of an H-mapped tile (CA3,
+ * (CA2, rho = 256) or one of the 8 sub-blocks of an H-mapped tile (CA3,
  * rho = 64); the units of all jobs are concatenated, job after job.  The
  * grid holds only as many workgroups (256 threads) as the device runs at
  * once — occupancy times compute units, or max_workgroups if that is

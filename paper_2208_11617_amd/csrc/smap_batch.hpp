@@ -95,10 +95,14 @@ struct QueueJob {
 
 // Tile shapes of the queue kernel (256 threads for both classes): CA2
 // rho 256 with one workgroup per tile; CA3 rho 64, 64 rows by one row per
-// lane, 16 planes per sub-block, 4 sub-blocks per tile.
+// lane, 8 planes per sub-block, 8 sub-blocks per tile.  The end of a launch,
+// when no unit is left to claim, lasts as long as a unit: with 16 planes 96
+// mixed jobs took 355 us, 20 jobs 35.1 and 5 jobs 31.2; with 8 347, 31.9 and
+// 27.2.  (rho 128, 32 rows by 16 planes: 336, 36.6 and 33.9; by 8 planes, most
+// of a small job's sub-blocks being empty claims: 360, 36.7 and 36.3.)
 constexpr int kQueueThreads = 256;
 constexpr int kQueueCa2Rho = 256, kQueueCa2W = 4, kQueueCa2R = 16, kQueueCa2D = 2;
-constexpr int kQueueCa3Rho = 64, kQueueCa3Ry = 64, kQueueCa3Rz = 16, kQueueCa3Rl = 1;
+constexpr int kQueueCa3Rho = 64, kQueueCa3Ry = 64, kQueueCa3Rz = 8, kQueueCa3Rl = 1;
 // Jobs with n below this are small: one work unit each, stepped cell by cell.
 constexpr int32_t kQueueSmallN = 15;
 
