@@ -115,7 +115,7 @@ struct Plan {
     uint32_t grid[3];            // launch grid of this launch (set per launch)
     Divu grid_div[2];            // division by grid[0], grid[1] (set per launch)
     uint32_t nwg;                // grid[0] * grid[1] * grid[2] (< 2^32)
-    uint32_t remap;              // workgroup order: 0 hardware, 1 xcd_remap, 2 xcd_scatter, 3 xcd_block
+    uint32_t remap;              // workgroup order (kOrder...)
     int32_t layout3;             // m = 3 native part: 0 packed grid, 1 one range per level
     uint32_t wg_base;            // first map index of this launch (0; a piece's start when
                                  // the pieces run as launches of their own)
@@ -150,19 +150,21 @@ SMAP_HD uint32_t xcd_scatter(uint32_t L, uint32_t nwg)
     return (L & ~7u) | ((L + h) & 7u);
 }
 
-// H launches of the 3-D automaton: L -> xcd_block(L) gives each XCD runs of 64
-// consecutive ids, the XCDs taking turns, so that sub-blocks that share halo
-// rows and the lines at the seams between their tiles meet in one L2 while all
-// XCDs still sweep the same part of the buffer together (contiguous eighths
-// lose that: n = 1024 193 us).  Plain order and runs of 8, 16, 32, 64, 128,
-// 256: n = 1024 178.8, 175.1, 171.9, 169.9, 168.8, 168.8, 174.7 us; n = 900
-// 128.0, 118.3, 116.0, 116.2, 114.1, 114.7, 115.3; level below n = 768.  Ids
-// past the last whole group of 512 stay.  A bijection of [0, nwg).
-SMAP_HD uint32_t xcd_block(uint32_t L, uint32_t nwg)
+// L -> xcd_block(L) gives each XCD runs of 2^lb consecutive ids, the XCDs
+// taking turns: neighbours that share lines and halo rows meet in one L2, as
+// under xcd_remap, while all XCDs still sweep the same part of the buffer
+// together, which contiguous eighths do not, so that the ends of the map fall
+// to all of them alike.  Ids past the last whole group of 8 runs stay.  A
+// bijection of [0, nwg).
+SMAP_HD uint32_t xcd_block(uint32_t L, uint32_t nwg, uint32_t lb)
 {
-    if ((L | 511u) >= nwg) return L;
-    return (L & ~511u) | ((L & 7u) << 6) | ((L >> 3) & 63u);
+    const uint32_t in = (8u << lb) - 1u;            // ids of a group of 8 runs, less one
+    if ((L | in) >= nwg) return L;
+    return (L & ~in) | ((L & 7u) << lb) | ((L >> 3) & ((1u << lb) - 1u));
 }
+
+// Plan::remap: the launch order (kOrderRuns + lb for xcd_block).
+constexpr uint32_t kOrderPlain = 0, kOrderContiguous = 1, kOrderScatter = 2, kOrderRuns = 3;
 
 #if defined(__HIPCC__)
 // Logical workgroup coordinates of this workgroup in the launch grid.
@@ -171,12 +173,15 @@ struct WgId {
 };
 __device__ __forceinline__ WgId wg_id(const Plan &P)
 {
-    if (P.remap) {
-        if (P.remap == 1 && P.grid[1] == 1 && P.grid[2] == 1)
-            return {xcd_remap(blockIdx.x, P.nwg), 0u, 0u};  // 1-D: no division
+    if (P.remap != kOrderPlain) {
+        const bool line = P.grid[1] == 1 && P.grid[2] == 1;   // 1-D: no division
+        if (P.remap == kOrderContiguous && line) return {xcd_remap(blockIdx.x, P.nwg), 0u, 0u};
+        if (P.remap >= kOrderRuns && line) return {xcd_block(blockIdx.x, P.nwg, P.remap - kOrderRuns), 0u, 0u};
         const uint32_t L = (blockIdx.z * P.grid[1] + blockIdx.y) * P.grid[0] + blockIdx.x;
-        const uint32_t g = P.remap == 1 ? xcd_remap(L, P.nwg)
-                                        : (P.remap == 2 ? xcd_scatter(L, P.nwg) : xcd_block(L, P.nwg));
+        const uint32_t g = P.remap == kOrderContiguous
+                               ? xcd_remap(L, P.nwg)
+                               : (P.remap == kOrderScatter ? xcd_scatter(L, P.nwg)
+                                                           : xcd_block(L, P.nwg, P.remap - kOrderRuns));
         const uint32_t r = divu(g, P.grid_div[0]), r2 = divu(r, P.grid_div[1]);
         return {g - r * P.grid[0], r - r2 * P.grid[1], r2};
     }

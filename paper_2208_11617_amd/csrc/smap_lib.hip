@@ -468,21 +468,27 @@ int dispatch(int m, int op, const TileCfg &tc, const Plan &P0, const void *in, v
     PL.nwg = grid.x * grid.y * grid.z;
     PL.grid_div[0] = make_divu(grid.x);
     PL.grid_div[1] = make_divu(grid.y);
-    // H runs XCD-contiguous (its workgroups are nearly all useful, so every
-    // XCD gets an equal share of the work) when neighbouring tiles share
-    // cache lines: the pointwise ops that touch memory.  Measured faster in
-    // the hardware order: MAP (no memory traffic to share) and the 2-D
-    // automaton (its sub-block order already spreads the concurrent workgroups
-    // over the buffer; 66.8 against 69.6 us at n = 16384).  The 3-D automaton
-    // takes runs of 64 ids per XCD (xcd_block).  BB never splits
+    // H's neighbouring tiles share cache lines, so its ids run over the XCDs
+    // in blocks of consecutive ones where memory is touched.  MAP keeps the
+    // plain order, and so does the 2-D automaton (its sub-blocks already sweep
+    // the buffer; runs of 8: level to 2 % faster on one machine, 3 % slower at
+    // n = 16384 on another).  Runs of 16 for the 3-D and 4-D pointwise ops (contiguous
+    // eighths, runs of 16: 4-D hash n = 128 34.7, 31.5 us, n = 100 21.4, 14.9;
+    // 3-D accum n = 600 149, 128, n = 400 58, 40), of 64 for the
+    // 3-D automaton (plain 178.8, 168.8 at n = 1024, 128.0, 114.1 at 900; runs of 8,
+    // 32, 128, 256: 175.1, 169.9, 168.8, 174.7 at 1024; level below n = 768).
+    // The 2-D pointwise ops run contiguous (runs of 64: accum n = 8000 67,
+    // 63 but hash 32.8, 34.7 and n = 4000 13.4, 14.3).  BB never splits
     // contiguously (the XCDs at the end of the range would get mostly empty
     // box tiles).  For the automata it scatters each group of 8 ids over
     // the XCDs: the plain order ties the useful tile columns to a few XCDs
     // when the box side shares a factor with 8 (3-D, n = 768-1023: 248-329
     // against 106-172 us).  The pointwise ops keep the plain order (4-D
     // hash: 29.9 against 34.7 us scattered).
-    PL.remap = BB ? ((op == OP_CA2 || op == OP_CA3) ? 2u : 0u)
-                  : (op == OP_CA3 ? 3u : ((op == OP_CA2 || op == OP_MAP) ? 0u : 1u));
+    if (BB) PL.remap = op == OP_CA2 || op == OP_CA3 ? kOrderScatter : kOrderPlain;
+    else if (op == OP_MAP || op == OP_CA2) PL.remap = kOrderPlain;
+    else if (op == OP_CA3) PL.remap = kOrderRuns + 6;
+    else PL.remap = m == 2 ? kOrderContiguous : kOrderRuns + 4;
     if (op == OP_CA2) {
         const uint8_t *i8 = (const uint8_t *)in;
         uint8_t *o8 = (uint8_t *)out;
@@ -1519,7 +1525,10 @@ int steps_launch(int m, int64_t n, int r, int beta, int op, int32_t steps, void 
     P.nwg = grid.x * grid.y * grid.z;
     P.grid_div[0] = make_divu(grid.x);
     P.grid_div[1] = make_divu(grid.y);
-    P.remap = bb ? 2u : 1u;
+    // runs of 64 per XCD (contiguous eighths, runs: n = 12000, 17 generations
+    // 59.8, 54.1 us, n = 20000, 17: 142.5, 131.7); a launch of few such runs
+    // keeps the eighths (n = 4000, 32: 16.7, 17.8)
+    P.remap = bb ? kOrderScatter : (P.nwg >= 2048 ? kOrderRuns + 6 : kOrderContiguous);
     hipStream_t s = (hipStream_t)stream;
     int left = steps;
     for (int i = 0; i < passes; ++i) {
