@@ -352,7 +352,7 @@ void launch_point_grp(const Plan &P, dim3 grid, const void *in, void *out, hipSt
 template <int OP, int RHO, int NT, int SUB, bool BB>
 void launch_rows(const Plan &P, dim3 grid, const void *in, void *out, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_rows<OP, RHO, NT, SUB, BB>), grid, dim3(NT), 0, s, P, (const uint32_t *)in, (uint32_t *)out);
+    hipLaunchKernelGGL((k_rows<RHO, OP, NT, SUB, BB>), grid, dim3(NT), 0, s, P, (const uint32_t *)in, (uint32_t *)out);
 }
 
 // ACCUM, HASH and EDM on 2-D tiles, one tile or part of a tile per workgroup.

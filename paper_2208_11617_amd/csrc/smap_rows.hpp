@@ -51,7 +51,7 @@ __device__ __forceinline__ float sqrt_rounded(float x)
     return r;
 }
 
-template <int OP, int RHO, int NT, int SUB, bool BB>
+template <int RHO, int OP, int NT, int SUB, bool BB>
 __global__ __launch_bounds__(NT) void k_rows(const Plan P, const uint32_t *in, uint32_t *out)
 {
     constexpr int G = RHO / 4;                   // lanes per tile row
