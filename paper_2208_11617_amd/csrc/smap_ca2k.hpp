@@ -38,20 +38,9 @@
 
 namespace smap {
 
-// Simplex cells of the 32 cells x .. x+31 of row y, as bits (cells left of
-// the box, x < 0, and past the hypotenuse cleared).
-__device__ __forceinline__ uint32_t ca2k_keep_bits(int32_t x, int32_t y, int32_t n)
-{
-    if (y < 0 || x <= -32) return 0u;
-    const int32_t hi = n - y - x + 1;               // cells x .. x+hi-1 satisfy x + y <= n
-    uint32_t m = hi >= 32 ? 0xFFFFFFFFu : (hi <= 0 ? 0u : (1u << hi) - 1u);
-    if (x < 0) m &= 0xFFFFFFFFu << (-x);            // the low -x cells are left of the box
-    return m;
-}
-
-// The two parts of the same mask for a column of words: the cells x .. x+31
-// with x >= 0, and, given those, the cells of row y of which number `last`
-// (possibly negative or beyond 31) is the last inside.  Branch-free.
+// Cells of a word inside the simplex, in two parts for a column of words: the
+// cells x .. x+31 with x >= 0, and, given those, the cells of row y of which
+// number `last` (possibly negative or beyond 31) is the last inside.
 __device__ __forceinline__ uint32_t ca2k_left_bits(int32_t x)
 {
     return x <= -32 ? 0u : ~0u << (min(max(-x, 0), 31));
@@ -62,11 +51,6 @@ __device__ __forceinline__ uint32_t ca2k_row_bits(uint32_t left, int32_t last, i
     const uint32_t none = (uint32_t)((last | y) >> 31);             // no cell at all
     return left & ~past & ~none;
 }
-
-// Four 0/1 bytes -> 4 bits (byte k -> bit k): the product places byte k's
-// bit at bit 24 + k, every other partial product lands on a distinct bit
-// below 24 or beyond bit 31, so nothing carries into bits 24..27.
-__device__ __forceinline__ uint32_t pack4(uint32_t d) { return ((d * 0x01020408u) >> 24) & 0xFu; }
 
 // 4 bits -> four 0/1 bytes (bit k -> byte k): bit k of v times 2^(7j)
 // lands on bit k + 7j, a multiple of 8 only for j = k, with no carries.

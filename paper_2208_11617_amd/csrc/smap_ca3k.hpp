@@ -34,7 +34,7 @@
 // Bound: the VALU at 16 generations (41 operations per 32 cells), HBM and the
 // load latency at 2.  n = 1024, 16 generations: 336 us (the form before, whole
 // 96^3 regions in LDS stepped one generation after another with one
-// workgroup a CU: 1409); n = 301, 8: 26 us (215, 35 workgroups).  A 128 x 128
+// workgroup a CU: 1409); n = 301, 8: 22 us (215, 35 workgroups).  A 128 x 128
 // plane and 16 waves are what the registers of a CU hold the sums of.
 #pragma once
 
