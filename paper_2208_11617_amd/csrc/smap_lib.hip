@@ -70,14 +70,19 @@ constexpr PointShape kPointShapes[] = {
 };
 
 // CA3 shapes: (rho, threads) -> rows RY (y), planes RZ (z), rows per lane RL.
-// Sub-blocks are 8 planes deep (4 and 16 measured slower at rho = 256).
+// Sub-blocks are 8 planes deep (4 and 16 measured slower at rho = 256), but 4
+// in the default shape below n = 768 and 2 in its launches below n = 320: there
+// a launch lasts about as long as a workgroup's planes, one after another.
+// us with 8, 4, 2 planes: n = 64 10.8, 7.0, 6.1; n = 200 11.9, 8.8, 8.3;
+// n = 300 14.7, 13.6, 13.1; n = 383 15.4, 14.1, 14.7; n = 512 32.3, 30.1, 32.5;
+// n = 700 66.1, 62.6, 68.7.
 struct Ca3Shape {
     int rho, wg, ry, rz, rl, sub;
 };
 constexpr int kCa3Rz = 8;
 constexpr int ca3_rz(int rho) { return kCa3Rz < rho ? kCa3Rz : rho; }
 constexpr Ca3Shape kCa3Shapes[] = {
-    {128, 256, 32, ca3_rz(128), 1, (128 / 32) * (128 / ca3_rz(128))},
+    {128, 256, 32, 4, 1, (128 / 32) * (128 / 4)},
     {128, 128, 16, ca3_rz(128), 1, (128 / 16) * (128 / ca3_rz(128))},
     {128, 512, 64, ca3_rz(128), 1, (128 / 64) * (128 / ca3_rz(128))},
     {256, 256, 16, ca3_rz(256), 1, (256 / 16) * (256 / ca3_rz(256))},
@@ -94,11 +99,15 @@ int op_class(int op) { return op == OP_CA2 ? 1 : (op == OP_CA3 ? 2 : 0); }
 // CA3: 256^3 tiles from n = 768 on; below, 128^3 (with only two or three
 // 256-cell tiles per side most of their sub-blocks fall outside the simplex)
 constexpr int64_t kCa3LargeTileN = 768;
+// the default shape's sub-blocks of 2 planes below this size
+constexpr int64_t kCa3ThinN = 320;
+constexpr int kCa3ThinSub = (128 / 32) * (128 / 2);
 
 TileCfg default_tile(int m, int64_t n, int cls)
 {
     if (cls == 1) return {1024, 64, 256};
     if (cls == 2) {  // the first listed shape of the tile side (256 threads)
+        if (n < kCa3ThinN) return {128, 256, kCa3ThinSub};
         const int rho = n >= kCa3LargeTileN ? 256 : 128;
         for (const Ca3Shape &c : kCa3Shapes)
             if (c.rho == rho) return {c.rho, c.wg, c.sub};
@@ -524,7 +533,10 @@ int dispatch(int m, int op, const TileCfg &tc, const Plan &P0, const void *in, v
             static_assert(Ca3Walk<RHO, RY, RZ, RL>::NT == WG, "CA3 shape");                      \
             launch_ca3<RHO, RY, RZ, RL, BB>(PL, grid, i8, o8, s);                                 \
             return kOk;
-        SMAP_CA3(128, 256, 32, ca3_rz(128), 1)
+        case 128 * 10000 + 256:
+            if (tc.sub == kCa3ThinSub) launch_ca3<128, 32, 2, 1, BB>(PL, grid, i8, o8, s);
+            else launch_ca3<128, 32, 4, 1, BB>(PL, grid, i8, o8, s);
+            return kOk;
         SMAP_CA3(128, 128, 16, ca3_rz(128), 1)
         SMAP_CA3(128, 512, 64, ca3_rz(128), 1)
         SMAP_CA3(256, 256, 16, ca3_rz(256), 1)

@@ -336,3 +336,17 @@ def test_job_array_fields():
     assert [(j.m, j.op, j.n, j.buf_in, j.buf_out) for j in arr] == [
         (2, smap.OP_CA2, 5, 1234, 5678), (3, smap.OP_CA3, -1, None, 7)]
     assert len(smap._job_array([])) == 1
+
+
+def test_ca3_default_sub_blocks():
+    """The 128-cell default splits a tile into sub-blocks of 2 planes below
+    n = 320 and of 4 from there on; the shape asked for by hand has 4."""
+    from paper_2208_11617_amd import binding as smap
+    for use_bb in (False, True):
+        assert smap.plan_info(3, 319, "ca3", use_bb=use_bb)["wgs_per_tile"] == 4 * 64
+        assert smap.plan_info(3, 320, "ca3", use_bb=use_bb)["wgs_per_tile"] == 4 * 32
+    try:
+        smap.set_tile(3, "ca3", 128, 256)
+        assert smap.plan_info(3, 100, "ca3")["wgs_per_tile"] == 4 * 32
+    finally:
+        smap.set_tile(3, "ca3", 0)
