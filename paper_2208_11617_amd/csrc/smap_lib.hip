@@ -165,7 +165,9 @@ struct CachedPlan {
     PlanCounts counts;
     int status;
 };
-std::map<std::tuple<int, int64_t, int, int, int, int, int>, CachedPlan> g_plans;  // (m,n,beta,rho,bb,cls,layout)
+// (m, n, beta, rho, sub-blocks, bb, class, layout): the status depends on the
+// workgroups, tiles times sub-blocks, not on the tiles alone
+std::map<std::tuple<int, int64_t, int, int, int, int, int, int>, CachedPlan> g_plans;
 // H native layout for m = 3 (simplex_set_layout); SMAP_LAYOUT_AUTO: the
 // level-ordered layout for one-job CA3 launches of one step and their plans,
 // the packed one for everything else
@@ -232,7 +234,7 @@ int plan_for(int m, int64_t n, int beta, bool bb, int cls, const TileCfg &t, Pla
     if (m == 3 && !bb)
         lay = g_layout3 != SMAP_LAYOUT_AUTO ? g_layout3
                                             : (one_job && cls == 2 ? SMAP_LAYOUT_LEVELS : SMAP_LAYOUT_PACKED);
-    auto key = std::make_tuple(m, n, bb ? 0 : beta, t.rho, bb ? 1 : 0, cls, lay);
+    auto key = std::make_tuple(m, n, bb ? 0 : beta, t.rho, t.sub, bb ? 1 : 0, cls, lay);
     auto it = g_plans.find(key);
     if (it == g_plans.end()) {
         CachedPlan cp{};
