@@ -1387,11 +1387,13 @@ void launch_ca2k(bool bb, const Plan &P, dim3 grid, const uint8_t *in, uint8_t *
 // to a CU) and the generations, not memory, are the time: they keep 77 % of
 // what they step where 256 keep 56 %.  (256, 512): n = 16384, 32 generations
 // 124, 109; n = 20000, 32: 189, 168; but n = 16384, 17: 85, 91; n = 11000, 32:
-// 73, 79 (325 tiles).
+// 73, 79 (325 tiles).  (Any pass of a board with more 256-cell regions than
+// half of what a launch can number takes 512 too.)
 int steps2_region(int64_t n, int gens)
 {
     const auto tiles = [&](int w) { const int64_t k = n / ca2k_rho(w, gens) + 1; return k * (k + 1) / 2; };
     if (tiles(128) * (gens + 8) <= 48000) return 128;
+    if (tiles(256) > (int64_t)kMaxWorkgroups / 2) return 512;
     return gens >= 24 && tiles(512) >= 600 ? 512 : 256;
 }
 
@@ -1526,14 +1528,17 @@ int steps_launch(int m, int64_t n, int r, int beta, int op, int32_t steps, void 
     int passes = (int)(((int64_t)steps + kh - 1) / kh);
     if (passes % 2 == 0) ++passes;
     const int gmax = (int)(((int64_t)steps + passes - 1) / passes);   // generations of the longest pass
-    // one plane and two rows within the 3-D kernels' 32-bit offsets
-    if (ca3 && (__int128)(n + 1) * (n + 3) + 64 >= ((__int128)1 << 32)) return kErange;
     // both run over 2-D tiles: the tiles of the 2-simplex, the columns of the 3-simplex
     Plan P;
     Steps3Plan S3;
-    const int w2 = steps2_region(n, gmax);
+    int w2 = 0;
     {
         std::lock_guard<std::mutex> lk(g_mu);
+        // The sizes taken do not depend on how a pass is cut: those whose 256-cell
+        // tiles, or 64-cell tiles in 3-D, a launch can number (and whose planes
+        // fit the 3-D kernels' 32-bit offsets).
+        rc = plan_for(m, n, bt, bb, ca3 ? 2 : 1, TileCfg{ca3 ? 64 : 256, 0, 1}, &P, nullptr, true);
+        if (rc != kOk) return rc;
         if (ca3) {
             auto it = g_steps3.find({n, gmax});
             if (it == g_steps3.end()) {
@@ -1544,6 +1549,7 @@ int steps_launch(int m, int64_t n, int r, int beta, int op, int32_t steps, void 
             if (rc == kOk && !bb && it->second.units.empty()) steps3_units(P, it->second);
             S3 = it->second;
         } else {
+            w2 = steps2_region(n, gmax);
             rc = plan_for(2, n, bt, bb, 1, TileCfg{ca2k_rho(w2, gmax), 0, 1}, &P, nullptr, true);
         }
     }
