@@ -117,6 +117,14 @@ TileCfg default_tile(int m, int64_t n, int cls)
     return {0, 0, 1};
 }
 
+// What a tuned choice of tile side, threads and grouping stands for: where it
+// names the default's, the default (whose sub-blocks depend on n).
+TileCfg tuned_tile(int m, int64_t n, int cls, const TileCfg &t)
+{
+    const TileCfg d = default_tile(m, n, cls);
+    return t.rho == d.rho && t.wg == d.wg && t.grp == d.grp ? d : t;
+}
+
 // The compiled shape of (m, class, rho, threads, tiles per workgroup);
 // *wg = 0 or *grp = 0 take the first listed match.  The automata have no
 // grouping (*grp must be 0 or 1).
@@ -1192,7 +1200,7 @@ int autotune(int m, int64_t n, int op, const void *in, void *out, int32_t reps, 
         int wg = r.wg_threads, sub = 1, grp = r.tiles_per_wg;
         if (tile_supported(m, cls, r.rho, &wg, &sub, &grp)) {
             std::lock_guard<std::mutex> lk(g_mu);
-            g_tuned[key] = Tuned{{r.rho, wg, sub, grp}, r.beta};
+            g_tuned[key] = Tuned{tuned_tile(m, n, cls, {r.rho, wg, sub, grp}), r.beta};
             *best = r;
             return kOk;
         }
@@ -1208,7 +1216,8 @@ int autotune(int m, int64_t n, int op, const void *in, void *out, int32_t reps, 
     simplex_tune_result top{0, 0, 0, 0.f, 1};
     bool have = false;
     rc = kOk;
-    for (const TileCfg &t : tile_candidates(m, cls)) {
+    for (const TileCfg &c : tile_candidates(m, cls)) {
+        const TileCfg t = tuned_tile(m, n, cls, c);
         for (int beta : betas) {
             {
                 std::lock_guard<std::mutex> lk(g_mu);
@@ -1239,7 +1248,7 @@ int autotune(int m, int64_t n, int op, const void *in, void *out, int32_t reps, 
     }
     int wg = top.wg_threads, sub = 1, grp = top.tiles_per_wg;
     tile_supported(m, cls, top.rho, &wg, &sub, &grp);
-    g_tuned[key] = Tuned{{top.rho, wg, sub, grp}, top.beta};
+    g_tuned[key] = Tuned{tuned_tile(m, n, cls, {top.rho, wg, sub, grp}), top.beta};
     *best = top;
     if (cache_path) {
         FILE *f = std::fopen(cache_path, "a");

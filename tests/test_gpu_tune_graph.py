@@ -166,3 +166,31 @@ def test_autotune_edm_skips_grouped_shapes(smap):
         assert torch.equal(again, ref)
     finally:
         smap.autotune_reset()
+
+
+@pytest.mark.parametrize("n,wgs_per_tile", [(100, 4 * 64), (319, 4 * 64), (320, 4 * 32)])
+def test_tuned_default_shape_is_the_default(smap, tmp_path, n, wgs_per_tile):
+    """A tuned 128-cell tile of 256 threads is the launch that goes by these
+    numbers untuned: sub-blocks of 2 planes below n = 320, of 4 from there on."""
+    inp = si.box_torch(3, n, "bern", 7400 + n, p=0.2, device="cuda")
+    out = si.sentinel_box_torch(3, n, True, device="cuda")
+    ref = out.clone()
+    default = smap.plan_info(3, n, "ca3")
+    smap.map_launch(3, n, "ca3", inp, ref)
+    cache = tmp_path / "tune"
+    try:
+        smap.autotune(3, n, "ca3", inp, out, reps=1, cache_path=str(cache))
+        field = cache.read_text().split()                # smap-tune-v2 device m n op rho threads ...
+        field[5:7] = ["128", "256"]
+        cache.write_text(" ".join(field) + "\n")
+        best = smap.autotune(3, n, "ca3", inp, out, reps=1, cache_path=str(cache))
+        assert (best["rho"], best["wg_threads"]) == (128, 256)
+        tuned = smap.plan_info(3, n, "ca3")
+        assert tuned["wgs_per_tile"] == wgs_per_tile
+        assert tuned == default
+        out.fill_(si.SENTINEL_U8)
+        smap.map_launch(3, n, "ca3", inp, out)
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref)
+    finally:
+        smap.autotune_reset()
