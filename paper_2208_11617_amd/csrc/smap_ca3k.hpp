@@ -44,11 +44,9 @@
 #include "smap_ca2.hpp"
 #include "smap_ca2k.hpp"
 #include "smap_decode.hpp"
+#include "smap_steps.hpp"
 
 namespace smap {
-
-// Generations of one pass at most.
-constexpr int kCa3kMaxGens = 16;
 
 // XW words (32 cells) and 32 XW rows a plane, R rows per lane, WPG waves per
 // generation.
@@ -67,14 +65,6 @@ struct Ca3kShape {
         return 64 * WPG * gens > CH ? 64 * WPG * gens : CH;
     }
 };
-
-// Pieces of one H launch: x tile, y tile (10 bits each) and piece (12 bits).
-constexpr int kCa3kUnits = 768;
-struct Ca3kUnits {
-    uint32_t unit[kCa3kUnits];
-};
-
-constexpr int ca3k_rho(int w, int gens) { return (w - 2 * gens) / 16 * 16; }
 
 // In-plane 3x3 sum q + 2 (k + t) + 4 m of 32 cells.
 struct Ca3kSum {

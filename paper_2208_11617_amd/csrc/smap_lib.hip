@@ -26,6 +26,7 @@
 #include "smap_point.hpp"
 #include "smap_rows.hpp"
 #include "smap_serve.hpp"
+#include "smap_steps.hpp"
 
 using namespace smap;
 
@@ -1431,89 +1432,6 @@ void dispatch_ca3k(int w, const Ca3kUnits *units, const Plan &P, dim3 grid, cons
     else launch_ca3k<2, 1, 2, false>(units, P, grid, in, out, gens, rz, s);
 }
 
-// Pieces of at most rz planes in the columns of rho x rho cells of Delta_n^3:
-// s + 1 columns are n - rho s + 1 planes high.
-int64_t steps3_pieces(int64_t n, int rho, int64_t rz)
-{
-    int64_t c = 0;
-    for (int64_t s = 0; s * rho <= n; ++s) c += (s + 1) * ((n - rho * s + rz) / rz);
-    return c;
-}
-
-// Launch plan of a pass of `gens` generations over Delta_n^3.
-struct Steps3Plan {
-    int w, rho, rz;                // region side, column side, planes of a piece at most
-    int64_t slots;                 // workgroups the chip holds at once
-    std::vector<uint32_t> units;   // H: the pieces (Ca3kUnits), tallest first
-};
-
-// W: 128-cell regions keep more of what they step; below n = 384 they leave
-// too few columns, and the planes of a generation, one after another, are the
-// time.  Measured (us; 64, 128): n = 200, 8 generations 19, 27 and 16: 42, 68;
-// n = 301: 27, 32 and 62, 76; n = 400: 40, 41 and 97, 89; n = 512: 56, 54.
-// rz: a workgroup fills a CU (two do with 64-cell regions and few
-// generations), and a pass over the chip takes the time of a piece, rz planes
-// and about 2 gens more to fill and drain the pipeline of generations; so the
-// pieces are made as tall as 1 to 8 whole rounds over the chip's 256 CUs allow,
-// whichever is shortest.  n = 1024, 16 generations: 340 us with 256
-// pieces, 372 with 512, 501 with 1024; 547 with pieces of 48 planes.
-Steps3Plan steps3_plan(int64_t n, int gens)
-{
-    Steps3Plan S;
-    S.w = n < 384 ? 64 : 128;
-    S.rho = ca3k_rho(S.w, gens);
-    S.slots = S.w == 64 && gens <= 4 ? 512 : 256;
-    int64_t best = 0;
-    for (int64_t r = 1; r <= 8; ++r) {
-        int64_t lo = 1, hi = n + 1;                  // the lowest pieces of which there are at most r rounds
-        while (lo < hi) {
-            const int64_t mid = (lo + hi) / 2;
-            if (steps3_pieces(n, S.rho, mid) <= r * S.slots) hi = mid;
-            else lo = mid + 1;
-        }
-        const int64_t cost = r * (lo + 2 * gens);
-        if (r == 1 || cost < best) {
-            best = cost;
-            S.rz = (int)lo;
-        }
-    }
-    return S;
-}
-
-// The pieces of an H pass from the host run of the H map over the columns (P:
-// its plan).  More than one round over the chip: tallest first.  One round:
-// every piece runs at once, and neighbouring columns share the lines at their
-// seams and their halos, so the pieces of one height index go row by row, an
-// eighth of them to each XCD (n = 900: 1 generation 137 -> 120 us, 8 151 -> 139,
-// 16 level; n = 512, 2: 34.5 -> 31.9).
-void steps3_units(const Plan &P, Steps3Plan &S)
-{
-    struct Piece {
-        int32_t height, k;
-        uint32_t x, y;
-    };
-    std::vector<Piece> v;
-    for (uint32_t w = 0; w < P.total; ++w) {
-        int32_t t[4] = {0, 0, 0, 0};
-        if (!decode_h<2>(P, w, t)) continue;
-        const int32_t height = P.n - P.rho * (t[0] + t[1]) + 1;
-        const int32_t pieces = (height + S.rz - 1) / S.rz, each = (height + pieces - 1) / pieces;
-        for (int32_t k = 0; k * each < height; ++k)
-            v.push_back({std::min(each, height - k * each), k, (uint32_t)t[0], (uint32_t)t[1]});
-    }
-    const bool once = (int64_t)v.size() <= S.slots;
-    if (once)
-        std::sort(v.begin(), v.end(), [](const Piece &a, const Piece &b) {
-            return std::tie(a.k, a.y, a.x) < std::tie(b.k, b.y, b.x);
-        });
-    else
-        std::stable_sort(v.begin(), v.end(), [](const Piece &a, const Piece &b) { return a.height > b.height; });
-    S.units.reserve(v.size());
-    for (uint32_t L = 0; L < v.size(); ++L) {
-        const Piece &q = v[once ? xcd_remap(L, (uint32_t)v.size()) : L];
-        S.units.push_back(q.x | q.y << 10 | (uint32_t)q.k << 20);
-    }
-}
 std::map<std::pair<int64_t, int>, Steps3Plan> g_steps3;   // (n, generations of the longest pass); g_mu held
 
 int steps_launch(int m, int64_t n, int r, int beta, int op, int32_t steps, void *a, void *b,

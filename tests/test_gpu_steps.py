@@ -187,3 +187,31 @@ def test_steps_3d_regions(smap, kind, n, steps):
     inside = (r.view(-1, 1, 1) + r.view(1, -1, 1) + r.view(1, 1, -1)) <= n
     assert torch.equal(out[inside], x[inside])
     assert bool((out[~inside] == si.SENTINEL_U8).all())
+
+
+@pytest.mark.parametrize("n,steps", [
+    # pieces of an H pass, 768 a launch: 1273; 1016 over a box beyond 4 GiB
+    (1250, 1), (1700, 3)])
+def test_steps_3d_several_launches_a_pass(smap, n, steps):
+    """Boxes whose pieces need more than one H launch a pass, H and BB against
+    single-step launches, plane by plane."""
+    r = torch.arange(n + 1, device="cuda", dtype=torch.int16)
+    s2 = r.view(-1, 1) + r
+    a = si.box_torch(3, n, "bern", 8400 + n, p=0.25, device="cuda", poison=False)
+    for z in range(n + 1):
+        a[z].masked_fill_(s2 > n - z, si.POISON_U8)
+    outs = {}
+    for kind in ("h", "bb"):
+        say(f"3-D {kind} n={n} steps={steps}")
+        outs[kind] = si.sentinel_box_torch(3, n, True, device="cuda")
+        (smap.map_launch_steps if kind == "h" else smap.bb_launch_steps)(3, n, "ca3", steps, a, outs[kind])
+        torch.cuda.synchronize()
+    x, y = a, si.sentinel_box_torch(3, n, True, device="cuda")
+    for _ in range(steps):
+        smap.map_launch(3, n, "ca3", x, y)
+        x, y = y, x
+    torch.cuda.synchronize()
+    for kind, out in outs.items():
+        for z in range(n + 1):
+            want = x[z].masked_fill(s2 > n - z, si.SENTINEL_U8)
+            assert torch.equal(out[z], want), (kind, z)
