@@ -183,9 +183,8 @@ std::map<std::tuple<int, int64_t, int, int, int, int, int, int>, CachedPlan> g_p
 int g_layout3 = SMAP_LAYOUT_AUTO;
 int g_general = 0;  // H launch of the pieces: 0 fused, 1 one launch per piece (simplex_set_general)
 
-// EDM: 64-cell tiles from n = 6000 on (four rows share a lane's points, and a
-// tile row is two lines): n = 8000 45 -> 35 us, 12000 84 -> 70, 16384
-// 162 -> 117; at n = 4000 15.4 and 15.5.
+// EDM: 64-cell tiles from n = 6000 on (us, 32 and 64 cells: n = 4300 11.5, 12.5;
+// 5200 15.2, 14.9; 7000 25.5, 24.7; 9000 36.2, 31.1; 12500 81, 61; 16384 140, 116).
 constexpr int64_t kEdmLargeTileN = 6000;
 
 TileCfg tile_for(int m, int64_t n, int op)
@@ -369,23 +368,61 @@ void launch_point_grp(const Plan &P, dim3 grid, const void *in, void *out, hipSt
                        (const uint32_t *)in, (uint32_t *)out);
 }
 
+// ACCUM, HASH and EDM on 2-D tiles: line-aligned parts of rows (k_rows) or whole
+// tile rows (k_point)?  Where every row of the box starts at a line the tile
+// rows are such parts already, without the offsets' cost (us, k_point, k_rows;
+// default shapes: ACCUM n = 8191 47.7, 52.8, BB 46.7, 51.7; EDM with 32-cell
+// tiles n = 4095 11.0, 11.9; only EDM on 64 cells and more, whose rows share a
+// lane's points, gains: 128-cell n = 2047 8.2, 6.5; HASH H on 32 cells is level).
+// Elsewhere a line written in parts costs little until the box outgrows the
+// caches, and k_rows, which walks one offset of the rows after another and a
+// row's head on top, has fewer rows in flight: the more so the wider the tile,
+// and EDM reads its rows' points through LDS, which a single row per lane
+// doesn't repay.  So k_rows from these sizes on, per op, map and tile side 16,
+// 32, 64, 128 (H below and above the line, k_point, k_rows: ACCUM 32 n = 2000 5.7,
+// 6.1, 2800 6.7, 6.5, 16000 391, 255; 64 n = 4300 13.4, 16.2, 7000 39.1, 37.2; 128
+// n = 4300 13.2, 19.3, 12500 166, 153; HASH 64 n = 4300 9.0, 11.9, 10000 38.2, 36.8;
+// 128 n = 6000 15.2, 18.2, 13500 99, 93; EDM 32 n = 2000 5.8, 6.6, 12500 81, 85,
+// 13500 138, 100; 64 n = 4300 12.5, 14.0, 8000 32.1, 28.8, 15000 171, 109).
+constexpr int64_t kRowsFrom[3][2][4] = {
+    {{3000, 2200, 6000, 11000}, {2000, 2000, 5000, 10000}},       // ACCUM: H, BB
+    {{12000, 0, 9000, 12000}, {0, 0, 6000, 12000}},               // HASH
+    {{13000, 13000, 5000, 7000}, {2000, 12500, 4000, 6000}},      // EDM
+};
+
+bool rows_route(int op, bool bb, int rho, const Plan &P, const void *out)
+{
+    if (P.stride[1] % 32 == 0 && (uintptr_t)out % 128 == 0)
+        return op == OP_EDM ? rho >= 64 : op == OP_HASH && rho == 32 && !bb;
+    return P.n >= kRowsFrom[op == OP_ACCUM ? 0 : (op == OP_HASH ? 1 : 2)][bb ? 1 : 0][ilog2c(rho) - 4];
+}
+
 template <int OP, int RHO, int NT, int SUB, bool BB>
 void launch_rows(const Plan &P, dim3 grid, const void *in, void *out, hipStream_t s)
 {
     hipLaunchKernelGGL((k_rows<RHO, OP, NT, SUB, BB>), grid, dim3(NT), 0, s, P, (const uint32_t *)in, (uint32_t *)out);
 }
 
-// ACCUM, HASH and EDM on 2-D tiles, one tile or part of a tile per workgroup.
+// ACCUM, HASH and EDM on 2-D tiles, one tile or part of a tile per workgroup:
+// whole tile rows or line-aligned parts of rows.  (EDM has no one-wave shape:
+// it runs the 256-thread one.)
 template <int OP, bool BB>
-int dispatch_rows(const TileCfg &tc, const Plan &P, dim3 grid, const void *in, void *out, hipStream_t s)
+int dispatch_2d(const TileCfg &tc, const Plan &P, dim3 grid, const void *in, void *out, hipStream_t s)
 {
-    if (tc.rho == 32 && tc.wg == 256) launch_rows<OP, 32, 256, 1, BB>(P, grid, in, out, s);
-    else if (tc.rho == 16) launch_rows<OP, 16, 64, 1, BB>(P, grid, in, out, s);
-    else if (tc.rho == 64) launch_rows<OP, 64, 256, 1, BB>(P, grid, in, out, s);
-    else if (tc.rho == 128) launch_rows<OP, 128, 256, 2, BB>(P, grid, in, out, s);
-    else if (OP == OP_EDM && tc.rho == 32) launch_rows<OP, 32, 256, 1, BB>(P, grid, in, out, s);
-    else return kEunsupported;
-    return kOk;
+    const bool rows = rows_route(OP, BB, tc.rho, P, out);
+    switch (tc.rho) {
+#define SMAP_2D(RHO, NT, SUB)                                                    \
+    case RHO:                                                                    \
+        if (rows) launch_rows<OP, RHO, NT, SUB, BB>(P, grid, in, out, s);        \
+        else launch_point<2, RHO, NT, SUB, OP, BB>(P, grid, in, out, s);         \
+        return kOk;
+    SMAP_2D(32, 256, 1)
+    SMAP_2D(16, 64, 1)
+    SMAP_2D(64, 256, 1)
+    SMAP_2D(128, 256, 2)
+#undef SMAP_2D
+    }
+    return kEunsupported;
 }
 
 template <int OP, bool BB>
@@ -434,21 +471,21 @@ template <bool BB>
 int dispatch_point(int op, int m, const TileCfg &tc, const Plan &P, dim3 grid, const void *in, void *out,
                    hipStream_t s)
 {
-    // (the one-wave and grouped 2-D shapes stay with the general kernels)
-    const bool rows = m == 2 && tc.grp == 1 && !(tc.rho == 32 && tc.wg != 256);
+    // the 2-D shapes of several waves and one tile a workgroup
+    const bool two_routes = m == 2 && tc.grp == 1 && !(tc.rho == 32 && tc.wg != 256);
     switch (op) {
     case OP_MAP: return dispatch_point_shape<OP_MAP, BB>(m, tc, P, grid, in, out, s);
     case OP_ACCUM:
-        if (rows) return dispatch_rows<OP_ACCUM, BB>(tc, P, grid, in, out, s);
+        if (two_routes) return dispatch_2d<OP_ACCUM, BB>(tc, P, grid, in, out, s);
         return dispatch_point_shape<OP_ACCUM, BB>(m, tc, P, grid, in, out, s);
     case OP_HITS: return dispatch_point_shape<OP_HITS, BB>(m, tc, P, grid, in, out, s);
     case OP_HASH:
-        if (rows) return dispatch_rows<OP_HASH, BB>(tc, P, grid, in, out, s);
+        if (two_routes) return dispatch_2d<OP_HASH, BB>(tc, P, grid, in, out, s);
         return dispatch_point_shape<OP_HASH, BB>(m, tc, P, grid, in, out, s);
     case OP_EDM:
         if (m != 2) return kEinval;
         if (tc.grp != 1) return kEunsupported;       // one tile per workgroup only
-        return dispatch_rows<OP_EDM, BB>(tc, P, grid, in, out, s);
+        return dispatch_2d<OP_EDM, BB>(tc, P, grid, in, out, s);
     }
     return kEinval;
 }

@@ -1,7 +1,8 @@
-// smap_point.hpp -- per-element kernels MAP, ACCUM, HITS, HASH (uint32).
+// smap_point.hpp -- per-element kernels MAP, ACCUM, HITS, HASH (uint32) and
+// EDM (float32, 2-D only).
 //
-// The test kernels of Section 5.1, Table tab:tests, plus HITS and HASH (on most
-// 2-D tiles ACCUM and HASH run in smap_rows.hpp instead, with EDM).
+// The test kernels of Section 5.1, Table tab:tests, plus HITS and HASH (larger
+// 2-D launches of ACCUM, HASH and EDM run in smap_rows.hpp instead).
 // The tile comes from the H decode (one 1-D grid over the fused native +
 // shell pieces) or from the BB grid coordinates; BB tiles fully outside the
 // simplex exit before touching memory.
@@ -14,6 +15,7 @@
 #include <stdint.h>
 
 #include "smap_decode.hpp"
+#include "smap_edm.hpp"
 
 namespace smap {
 
@@ -59,7 +61,7 @@ __device__ __forceinline__ uint32_t hash32_words(const int32_t *x)
 // hpre[j] is the FNV-1a state after words x_1 + j, x_2 .. x_KF, common to
 // the lane's rows.
 template <int M, int OP, int KF = 0>
-__device__ __forceinline__ void point_lane(const uint32_t *pin, uint32_t *pout,
+__device__ __forceinline__ void point_lane(int32_t n, const uint32_t *in, const uint32_t *pin, uint32_t *pout,
                                            uint32_t off, int32_t v, int32_t (&xr)[M],
                                            const uint32_t (&hpre)[4] = {0u, 0u, 0u, 0u})
 {
@@ -81,6 +83,33 @@ __device__ __forceinline__ void point_lane(const uint32_t *pin, uint32_t *pout,
             }
 #pragma unroll
             for (int j = 0; j < 4; ++j) r[j] += 1u;
+        } else if constexpr (OP == OP_EDM) {
+            static_assert(M == 2, "EDM is 2-D");
+            const float *pts = reinterpret_cast<const float *>(in), *q = pts + 3 * (int64_t)(n - xr[1]);
+            const float *p = pts + 3 * (int64_t)xr[0];
+            float px[4], py[4], pz[4];
+            if (v >= 4) {  // points i0 .. i0+3: 12 floats, 16-byte aligned (i0 % 4 == 0)
+                const float4 a = reinterpret_cast<const float4 *>(p)[0], b = reinterpret_cast<const float4 *>(p)[1],
+                             c = reinterpret_cast<const float4 *>(p)[2];
+                px[0] = a.x; py[0] = a.y; pz[0] = a.z;
+                px[1] = a.w; py[1] = b.x; pz[1] = b.y;
+                px[2] = b.z; py[2] = b.w; pz[2] = c.x;
+                px[3] = c.y; py[3] = c.z; pz[3] = c.w;
+            } else {       // only the points inside: no read past point n
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int k = j < v ? 3 * j : 0;
+                    px[j] = p[k]; py[j] = p[k + 1]; pz[j] = p[k + 2];
+                }
+            }
+            float s[4];
+            if (edm_tiny(edm_squares(px, py, pz, q[0], q[1], q[2], s))) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) r[k] = __float_as_uint(sqrtf(s[k]));
+            } else {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) r[k] = __float_as_uint(sqrt_rounded(s[k]));
+            }
         } else if constexpr (KF > 0) {  // OP_HASH from the lane's common leading words
 #pragma unroll
             for (int j = 0; j < 4; ++j) r[j] = hash32_fmix(hash32_state<KF, M>(hpre[j], xr));
@@ -165,7 +194,7 @@ __global__ __launch_bounds__(NT) void k_point(const Plan P, const uint32_t *in, 
         }
         const int32_t v = n - rs + 1;                // elements of the lane inside the simplex
         if (v <= 0) continue;
-        point_lane<M, OP>(pin, pout, off, v, xr);
+        point_lane<M, OP>(n, in, pin, pout, off, v, xr);
     }
 }
 
@@ -274,7 +303,7 @@ __global__ __launch_bounds__(NT) void k_point_grp(const Plan P, const uint32_t *
         }
         const int32_t v = n - rs + 1;
         if (v <= 0) continue;
-        point_lane<M, OP, OP == OP_HASH ? KF : 0>(pin, pout, off, v, xr, hpre);
+        point_lane<M, OP, OP == OP_HASH ? KF : 0>(n, in, pin, pout, off, v, xr, hpre);
     }
 }
 

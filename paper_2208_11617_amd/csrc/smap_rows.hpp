@@ -1,23 +1,21 @@
 // smap_rows.hpp -- ACCUM, HASH and EDM on Delta_n^2 in line-aligned parts of
 // rows.
 //
-// EDM (Section 5.1): element (x_1, x_2) holds the distance of points i = x_1
-// and j = n - x_2 of a set of n+1 points in R^3 (x_1 + x_2 <= n is i <= j), in
-// float32: three differences, a sum of squares, a correctly rounded square
-// root.  ACCUM and HASH as in smap_point.hpp.  The tile comes from the H decode
-// or the BB grid.
+// EDM as in smap_edm.hpp, ACCUM and HASH as in smap_point.hpp, whose k_point is
+// the route of smaller boxes and of those whose rows start at lines.  The tile
+// comes from the H decode or the BB grid.
 //
 // All three are bound by HBM writes, and those by whole 128-byte lines: a line
 // that two workgroups write part by part, from different L2s, costs about
-// twice (n = 16384, 537 MB: 5.2 TB/s where the rows happen to start on lines,
-// 3.3 TB/s where they don't, a fill 6.9).  A row of the box starts at any
-// element.  So the part of a row that a tile writes starts up to a line after
-// the tile does, at a line's start, and ends as much later; the elements before
-// a row's first whole line are its first tile's.  At n = 16384: EDM 148 -> 117
-// us, HASH 138 -> 115, ACCUM 247 -> 228; n = 8000: 52 -> 35, 49 -> 34,
-// 93 -> 68.  (Aligned to 32 or 64 bytes only, EDM took 136 and 127 us; it also
-// loaded its points for every row and used a root that scales its argument
-// first, which by themselves were worth 10 us.)
+// twice once the box outgrows the caches (n = 16384, 537 MB: 5.2 TB/s where the
+// rows happen to start on lines, 3.3 TB/s where they don't, a fill 6.9).  A row
+// of the box starts at any element.  So the part of a row that a tile writes
+// starts up to a line after the tile does, at a line's start, and ends as much
+// later; the elements before a row's first whole line are its first tile's.
+// Default tiles, k_point and this (us): n = 16384 EDM 129, 116, HASH 131, 114,
+// ACCUM 240, 225; n = 16000 EDM 210, 119, HASH 245, 125, ACCUM 391, 255; n = 8000
+// HASH 31.9, 27.9, ACCUM 77, 61.  (Aligned to 32 or 64 bytes only, EDM at n =
+// 16384 took 136 and 127 us.)
 //
 // A lane owns 4 consecutive x_1 (one 16-byte store); in rows kAlign apart the
 // parts start at the same offset from the tile, so the lane keeps what depends
@@ -29,27 +27,10 @@
 #include <stdint.h>
 
 #include "smap_decode.hpp"
+#include "smap_edm.hpp"
 #include "smap_point.hpp"
 
 namespace smap {
-
-// sqrt(x) correctly rounded, for x = 0, x >= 2^-96, infinity or NaN.  The
-// hardware's square root s is within one unit u in the last place.  Of s - u, s
-// and s + u the nearest to the root is s - u where x < (s - u/2)^2 =
-// s (s - u) + u^2/4 and s + u where x > s (s + u) + u^2/4; floats that near
-// are whole multiples of u^2, as the products are, so x <= s (s - u) and
-// x > s (s + u) say the same, and a fused multiply-add gives each difference's
-// sign exactly (from 2^-96 on it cannot underflow).  For 0, infinity and NaN
-// both comparisons fail and s is the answer.
-__device__ __forceinline__ float sqrt_rounded(float x)
-{
-    const float s = __builtin_amdgcn_sqrtf(x);
-    const float lo = __uint_as_float(__float_as_uint(s) - 1u), hi = __uint_as_float(__float_as_uint(s) + 1u);
-    const float below = __builtin_fmaf(-lo, s, x), above = __builtin_fmaf(-hi, s, x);
-    float r = below <= 0.0f ? lo : s;
-    r = above > 0.0f ? hi : r;
-    return r;
-}
 
 template <int RHO, int OP, int NT, int SUB, bool BB>
 __global__ __launch_bounds__(NT) void k_rows(const Plan P, const uint32_t *in, uint32_t *out)
@@ -114,14 +95,7 @@ __global__ __launch_bounds__(NT) void k_rows(const Plan P, const uint32_t *in, u
             if constexpr (OP == OP_EDM) {
                 const float4 q = rowpt[r];
                 float s[4];
-                uint32_t tiny = ~0u;                     // least nonzero square, as bits minus one
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const float dx = px[k] - q.x, dy = py[k] - q.y, dz = pz[k] - q.z;
-                    s[k] = __builtin_fmaf(dz, dz, __builtin_fmaf(dx, dx, dy * dy));
-                    tiny = min(tiny, __float_as_uint(s[k]) - 1u);
-                }
-                if (tiny < 0x0F7FFFFFu) {                // a square below 2^-96: the scaled root
+                if (edm_tiny(edm_squares(px, py, pz, q.x, q.y, q.z, s))) {
 #pragma unroll
                     for (int k = 0; k < 4; ++k) d[k] = __float_as_uint(sqrtf(s[k]));
                 } else {
