@@ -187,6 +187,19 @@ __device__ __forceinline__ WgId wg_id(const Plan &P)
     }
     return {blockIdx.x, blockIdx.y, blockIdx.z};
 }
+// The same for the per-element kernels: H's grid is a line of workgroups in
+// plain order, eighths or runs, BB keeps the plain order.  (The general form's
+// divisions beside the decodes of several tiles a workgroup, which fill the
+// scalar registers, cost spills: 4-D hash, 16 4-cell tiles, n = 8 13.8 us, 12.5
+// with this; 2 8-cell tiles, n = 20 5.14, 4.90.)
+template <bool BB>
+__device__ __forceinline__ WgId wg_id_point(const Plan &P)
+{
+    if (BB) return {blockIdx.x, blockIdx.y, blockIdx.z};
+    if (P.remap == kOrderContiguous) return {xcd_remap(blockIdx.x, P.nwg), 0u, 0u};
+    if (P.remap >= kOrderRuns) return {xcd_block(blockIdx.x, P.nwg, P.remap - kOrderRuns), 0u, 0u};
+    return {blockIdx.x, 0u, 0u};
+}
 #endif
 
 #if defined(__HIPCC__)

@@ -154,11 +154,11 @@ __global__ __launch_bounds__(NT) void k_point(const Plan P, const uint32_t *in, 
     int32_t t[4] = {0, 0, 0, 0};
     uint32_t sub;
     if (BB) {
-        const WgId g = wg_id(P);
+        const WgId g = wg_id_point<BB>(P);
         decode_bb(P, g.x, g.y, g.z / SUB, t);
         sub = g.z % SUB;
     } else {
-        const WgId g = wg_id(P);
+        const WgId g = wg_id_point<BB>(P);
         if (!decode_h<M>(P, g.x / SUB, t)) return;
         sub = g.x % SUB;
     }
@@ -235,7 +235,7 @@ __global__ __launch_bounds__(NT) void k_point_grp(const Plan P, const uint32_t *
     const int32_t n = P.n;
     int32_t tx[M][U];
     bool tv[U];
-    const WgId g = wg_id(P);
+    const WgId g = wg_id_point<BB>(P);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         int32_t t[4] = {0, 0, 0, 0};

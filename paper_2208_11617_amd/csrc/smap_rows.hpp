@@ -44,7 +44,7 @@ __global__ __launch_bounds__(NT) void k_rows(const Plan P, const uint32_t *in, u
                   "bad row shape");
     int32_t t[4] = {0, 0, 0, 0};
     uint32_t sub;
-    const WgId g = wg_id(P);
+    const WgId g = wg_id_point<BB>(P);
     if (BB) {
         decode_bb(P, g.x, g.y, 0, t);
         sub = g.z;
