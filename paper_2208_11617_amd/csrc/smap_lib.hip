@@ -1431,17 +1431,19 @@ void launch_ca2k(bool bb, const Plan &P, dim3 grid, const uint8_t *in, uint8_t *
 // n = 5000, 17: 21.1, 22.8 (1984); n = 3001, 32: 22.8, 21.6 (1104 of 64);
 // n = 8191, 8: 17.5, 19.4 (2738 of 112); n = 8191, 17: 42.5, 33.5 (5253).
 // 512 cells where the board fills the chip with such tiles (two of 448 cells
-// to a CU) and the generations, not memory, are the time: they keep 77 % of
-// what they step where 256 keep 56 %.  (256, 512): n = 16384, 32 generations
-// 124, 109; n = 20000, 32: 189, 168; but n = 16384, 17: 85, 91; n = 11000, 32:
-// 73, 79 (325 tiles).  (Any pass of a board with more 256-cell regions than
+// to a CU) and the 256-cell regions' tiles are down to 192 cells, from 25
+// generations on: 512 then keep 77 % of what they step, 256 keep 56 %.  (256,
+// 512), 32 generations: n = 12000 66, 74 (378 tiles); n = 14800 97, 99 (595); n =
+// 15232 104, 101 (630); n = 16384 117, 102 (703); n = 20000 176, 162; with 24 (208
+// of 256 cells kept a side): n = 16000 78, 86; n = 16384 85, 87; n = 20000 131, 139.
+// (Any pass of a board with more 256-cell regions than
 // half of what a launch can number takes 512 too.)
 int steps2_region(int64_t n, int gens)
 {
     const auto tiles = [&](int w) { const int64_t k = n / ca2k_rho(w, gens) + 1; return k * (k + 1) / 2; };
     if (tiles(128) * (gens + 8) <= 48000) return 128;
     if (tiles(256) > (int64_t)kMaxWorkgroups / 2) return 512;
-    return gens >= 24 && tiles(512) >= 600 ? 512 : 256;
+    return ca2k_rho(256, gens) <= 192 && tiles(512) >= 600 ? 512 : 256;
 }
 
 // CA3: a workgroup's region is W x W cells (Ca3kShape) and streams rz planes.

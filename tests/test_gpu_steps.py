@@ -215,3 +215,17 @@ def test_steps_3d_several_launches_a_pass(smap, n, steps):
         for z in range(n + 1):
             want = x[z].masked_fill(s2 > n - z, si.SENTINEL_U8)
             assert torch.equal(out[z], want), (kind, z)
+
+
+@pytest.mark.parametrize("kind", ["h", "bb"])
+def test_steps_widest_regions_from_25(smap, kind):
+    """25 generations, the fewest that take 512-cell regions, against one step and 24."""
+    n = 15800
+    a = si.box_torch(2, n, "bern", 8250, p=0.35, device="cuda")
+    launch = smap.map_launch_steps if kind == "h" else smap.bb_launch_steps
+    x, y, out = (si.sentinel_box_torch(2, n, True, device="cuda") for _ in range(3))
+    smap.map_launch(2, n, "ca2", a, x)
+    launch(2, n, "ca2", 24, x, y)
+    launch(2, n, "ca2", 25, a, out)
+    torch.cuda.synchronize()
+    assert torch.equal(out, y)
