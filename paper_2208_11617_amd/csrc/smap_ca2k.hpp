@@ -33,67 +33,11 @@
 
 #include <type_traits>
 
+#include "smap_bits.hpp"
 #include "smap_ca2.hpp"
 #include "smap_decode.hpp"
 
 namespace smap {
-
-// Cells of a word inside the simplex, in two parts for a column of words: the
-// cells x .. x+31 with x >= 0, and, given those, the cells of row y of which
-// number `last` (possibly negative or beyond 31) is the last inside.
-__device__ __forceinline__ uint32_t ca2k_left_bits(int32_t x)
-{
-    return x <= -32 ? 0u : ~0u << (min(max(-x, 0), 31));
-}
-__device__ __forceinline__ uint32_t ca2k_row_bits(uint32_t left, int32_t last, int32_t y)
-{
-    const uint32_t past = 0xFFFFFFFEu << min(max(last, 0), 31);     // the cells after the last
-    const uint32_t none = (uint32_t)((last | y) >> 31);             // no cell at all
-    return left & ~past & ~none;
-}
-
-// 4 bits -> four 0/1 bytes (bit k -> byte k): bit k of v times 2^(7j)
-// lands on bit k + 7j, a multiple of 8 only for j = k, with no carries.
-__device__ __forceinline__ uint32_t unpack4(uint32_t v) { return ((v & 0xFu) * 0x00204081u) & 0x01010101u; }
-
-// Sixteen bytes -> 16 bits, bit k = bit 0 of byte k: dot products of the
-// 0/1 bytes with powers of two, eight bytes per accumulator.
-__device__ __forceinline__ uint32_t pack16(const uint4 &v)
-{
-    uint32_t lo = __builtin_amdgcn_udot4(v.x & 0x01010101u, 0x08040201u, 0u, false);
-    lo = __builtin_amdgcn_udot4(v.y & 0x01010101u, 0x80402010u, lo, false);
-    uint32_t hi = __builtin_amdgcn_udot4(v.z & 0x01010101u, 0x08040201u, 0u, false);
-    hi = __builtin_amdgcn_udot4(v.w & 0x01010101u, 0x80402010u, hi, false);
-    return lo | (hi << 8);
-}
-
-// One 3-input logic operation; the immediate is the function of the bit
-// patterns A, B, C (of the three inputs).
-constexpr uint32_t kBitA = 0xF0u, kBitB = 0xCCu, kBitC = 0xAAu;
-template <uint32_t F>
-__device__ __forceinline__ uint32_t bit3(uint32_t a, uint32_t b, uint32_t c)
-{
-    return __builtin_amdgcn_bitop3_b32(a, b, c, F & 0xFFu);
-}
-__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) { return bit3<kBitA ^ kBitB ^ kBitC>(a, b, c); }
-__device__ __forceinline__ uint32_t maj3(uint32_t a, uint32_t b, uint32_t c)
-{
-    return bit3<(kBitA & kBitB) | (kBitC & (kBitA ^ kBitB))>(a, b, c);
-}
-
-// B3/S23 on 32 cells: the horizontal 3-sums (lo, hi bits) of the rows above,
-// at and below them, and the cells themselves.  The 3x3 sum with the centre is
-// T = a + 2 (k + b) + 4 m; next = (T == 3) | (T == 4 & alive).
-__device__ __forceinline__ uint32_t life_bits(uint32_t p0, uint32_t p1, uint32_t c0, uint32_t c1, uint32_t n0,
-                                              uint32_t n1, uint32_t alive)
-{
-    const uint32_t a = xor3(p0, c0, n0), k = maj3(p0, c0, n0);
-    const uint32_t b = xor3(p1, c1, n1), m = maj3(p1, c1, n1);
-    const uint32_t t3 = bit3<(kBitA ^ kBitB) & ~kBitC>(k, b, m);                  // T - a == 2
-    const uint32_t t4 = bit3<~(kBitA ^ kBitB) & (kBitA ^ kBitC)>(k, b, m);        // T - a == 4
-    const uint32_t s = t4 & alive;
-    return bit3<(kBitA & kBitB) | (~kBitA & kBitC)>(a, t3, s);
-}
 
 // Generations of one pass at most.
 constexpr int kCa2kMaxGens = 32;
@@ -168,7 +112,7 @@ __device__ __forceinline__ void ca2k_tile(const Plan &P, const uint8_t *__restri
             for (int k = 0; k < LB; ++k) {
                 const int r = r0 + k * RPI + rt;
                 const int32_t yr = ys + r;
-                const uint32_t w = (pack16(v[k]) << up16) & ca2k_row_bits(left, n - yr - xc, yr);
+                const uint32_t w = (pack16(v[k].x, v[k].y, v[k].z, v[k].w) << up16) & ca2k_row_bits(left, n - yr - xc, yr);
                 reinterpret_cast<uint16_t *>(&stage[r][0])[threadIdx.x % (2 * XL)] = (uint16_t)w;
             }
         }

@@ -41,6 +41,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "smap_bits.hpp"
 #include "smap_ca2.hpp"
 #include "smap_ca2k.hpp"
 #include "smap_decode.hpp"
@@ -65,33 +66,6 @@ struct Ca3kShape {
         return 64 * WPG * gens > CH ? 64 * WPG * gens : CH;
     }
 };
-
-// In-plane 3x3 sum q + 2 (k + t) + 4 m of 32 cells.
-struct Ca3kSum {
-    uint32_t q, k, t, m;
-};
-
-// B6/S567 from three planes' sums and the cells themselves (which are dead
-// outside `left`); the result's bits outside `left` and `keep` are cleared.
-__device__ __forceinline__ uint32_t ca3k_rule(const Ca3kSum &a, const Ca3kSum &b, const Ca3kSum &c, uint32_t alive,
-                                              uint32_t left, uint32_t keep)
-{
-    // T = t0 + 2 t1 + 4 t2 + 8 t3 + 16 t4 (at most 27, the centre included)
-    const uint32_t t0 = xor3(a.q, b.q, c.q), u = maj3(a.q, b.q, c.q);
-    const uint32_t k = xor3(a.k, b.k, c.k), ck = maj3(a.k, b.k, c.k);
-    const uint32_t t = xor3(a.t, b.t, c.t), ct = maj3(a.t, b.t, c.t);
-    const uint32_t t1 = xor3(u, k, t), cu = maj3(u, k, t);
-    const uint32_t m = xor3(a.m, b.m, c.m), cm = maj3(a.m, b.m, c.m);
-    const uint32_t v = xor3(ck, ct, cu), cv = maj3(ck, ct, cu);
-    const uint32_t t2 = m ^ v, cw = m & v;
-    const uint32_t t3 = xor3(cm, cv, cw), t4 = maj3(cm, cv, cw);
-    const uint32_t e67 = bit3<kBitA & kBitB & ~kBitC>(t1, t2, t3);          // T = 6 or 7 (mod 16)
-    const uint32_t e89 = bit3<~kBitA & ~kBitB & kBitC>(t1, t2, t3);         // T = 8 or 9
-    const uint32_t born = bit3<kBitA & ~kBitB & kBitC>(e67, t0, left);      // T = 6
-    const uint32_t stay = bit3<kBitA | (kBitB & ~kBitC)>(e67, e89, t0);     // T = 6, 7 or 8
-    const uint32_t next = bit3<(kBitA & kBitB) | (~kBitA & kBitC)>(alive, stay, born);
-    return bit3<kBitA & ~kBitB & kBitC>(next, t4, keep);
-}
 
 template <int XW, int R, int WPG, bool SAFE>
 __device__ __forceinline__ void ca3k_tile(const Plan &P, const uint8_t *__restrict__ in, uint8_t *__restrict__ out,
@@ -146,7 +120,7 @@ __device__ __forceinline__ void ca3k_tile(const Plan &P, const uint8_t *__restri
     };
     const int lat = (lr / R) * GP + (lr % R) * XW + lc / 2;   // LDS word of the piece
     auto commit = [&](int32_t z, const uint4 &v, int slot) {
-        const uint32_t w = (pack16(v) << lup) & ca2k_row_bits(lleft, n - z - ly - lx, ly);
+        const uint32_t w = (pack16(v.x, v.y, v.z, v.w) << lup) & ca2k_row_bits(lleft, n - z - ly - lx, ly);
         reinterpret_cast<uint16_t *>(&buf[slot][0][lat])[lc % 2] = (uint16_t)w;
     };
 
