@@ -381,12 +381,13 @@ void launch_point_grp(const Plan &P, dim3 grid, const void *in, void *out, hipSt
 // doesn't repay.  So k_rows from these sizes on, per op, map and tile side 16,
 // 32, 64, 128 (H below and above the line, k_point, k_rows: ACCUM 32 n = 2000 5.7,
 // 6.1, 2800 6.7, 6.5, 16000 391, 255; 64 n = 4300 13.4, 16.2, 7000 39.1, 37.2; 128
-// n = 4300 13.2, 19.3, 12500 166, 153; HASH 64 n = 4300 9.0, 11.9, 10000 38.2, 36.8;
-// 128 n = 6000 15.2, 18.2, 13500 99, 93; EDM 32 n = 2000 5.8, 6.6, 12500 81, 85,
-// 13500 138, 100; 64 n = 4300 12.5, 14.0, 8000 32.1, 28.8, 15000 171, 109).
+// n = 4300 13.2, 19.3, 12500 166, 153; HASH 32 level below 2000, 8000 31.9, 27.9; 64
+// n = 4300 9.0, 11.9, 10000 38.2, 36.8; 128 n = 6000 15.2, 18.2, 13500 99, 93; EDM 32
+// n = 2000 5.8, 6.6, 12500 81, 85, 13500 138, 100; 64 n = 4300 12.5, 14.0, 8000 32.1,
+// 28.8, 15000 171, 109).
 constexpr int64_t kRowsFrom[3][2][4] = {
     {{3000, 2200, 6000, 11000}, {2000, 2000, 5000, 10000}},       // ACCUM: H, BB
-    {{12000, 0, 9000, 12000}, {0, 0, 6000, 12000}},               // HASH
+    {{12000, 2000, 9000, 12000}, {0, 0, 6000, 12000}},            // HASH
     {{13000, 13000, 5000, 7000}, {2000, 12500, 4000, 6000}},      // EDM
 };
 

@@ -72,7 +72,7 @@ def check(smap, op, n, launch, off):
 
 # the sizes from which H and BB take the row parts, per tile side
 FROM = {"accum": {16: (3000, 2000), 32: (2200, 2000), 64: (6000, 5000), 128: (11000, 10000)},
-        "hash": {16: (12000, 100), 32: (100, 100), 64: (9000, 6000), 128: (12000, 12000)},
+        "hash": {16: (12000, 100), 32: (2000, 100), 64: (9000, 6000), 128: (12000, 12000)},
         "edm": {16: (13000, 2000), 32: (13000, 12500), 64: (5000, 4000), 128: (7000, 6000)}}
 
 
