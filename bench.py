@@ -34,7 +34,7 @@ BYTES_PER_ELEMENT = {"accum": 8, "ca2": 2, "ca3": 2, "hash": 4, "hits": 8, "map"
 KERNEL_SOURCES = {
     "ca2": ["smap_decode.hpp", "smap_ca2.hpp"],
     "ca3": ["smap_decode.hpp", "smap_ca2.hpp", "smap_ca3.hpp"],
-    "point": ["smap_decode.hpp", "smap_point.hpp", "smap_rows.hpp"],
+    "point": ["smap_decode.hpp", "smap_point.hpp", "smap_rows.hpp", "smap_edm.hpp", "smap_bits.hpp"],
     "copy": ["smap_copy.hpp"],
 }
 

@@ -71,9 +71,10 @@ constexpr PointShape kPointShapes[] = {
 };
 
 // CA3 shapes: (rho, threads) -> rows RY (y), planes RZ (z), rows per lane RL.
-// Sub-blocks are 8 planes deep (4 and 16 measured slower at rho = 256), but 4
-// in the default shape below n = 768 and 2 in its launches below n = 320: there
-// a launch lasts about as long as a workgroup's planes, one after another.
+// Sub-blocks are 8 planes deep (rho = 256, H, us with 8, 4, 16 planes: n = 768 89,
+// 97, 94; n = 900 114, 123, 122; n = 1000 148, 149, 155; n = 1024 169, 164, 176),
+// but 4 in the default shape below n = 768 and 2 in its launches below n = 320:
+// there a launch lasts about as long as a workgroup's planes, one after another.
 // us with 8, 4, 2 planes: n = 64 10.8, 7.0, 6.1; n = 200 11.9, 8.8, 8.3;
 // n = 300 14.7, 13.6, 13.1; n = 383 15.4, 14.1, 14.7; n = 512 32.3, 30.1, 32.5;
 // n = 700 66.1, 62.6, 68.7.

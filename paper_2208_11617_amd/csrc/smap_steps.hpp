@@ -42,8 +42,9 @@ struct Steps3Plan {
 
 // W: 128-cell regions keep more of what they step; below n = 384 they leave
 // too few columns, and the planes of a generation, one after another, are the
-// time.  Measured (us; 64, 128): n = 200, 8 generations 19, 27 and 16: 42, 68;
-// n = 301: 27, 32 and 62, 76; n = 400: 40, 41 and 97, 89; n = 512: 56, 54.
+// time.  Measured (us; 64, 128): n = 200, 8 generations 16, 25 and 16: 36, 64;
+// n = 301: 22, 29 and 51, 72; n = 400: 32, 36 and 81, 83; n = 450: 39, 40 and 112,
+// 91; n = 512: 50, 46 and 166, 105.
 // rz: a workgroup is counted as filling a CU (two do with 64-cell regions and
 // up to 4 generations; with more, and with 128-cell regions up to 4, two would
 // fit as well, but are not counted on), and a pass over the chip takes the time of a piece, rz planes
